@@ -3,6 +3,7 @@
 // the step loop and of the transforms.
 #pragma once
 
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <vector>
@@ -45,6 +46,31 @@ inline float bf16_value_of(float v) {
     float r;
     std::memcpy(&r, &u, 4);
     return r;
+}
+
+// f16 bits of v, round to nearest even (finite values past its range become
+// infinities, NaN stays one).
+inline uint16_t f16_round(float v) {
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    const uint32_t s = (u >> 16) & 0x8000u;
+    u &= 0x7fffffffu;
+    if (u > 0x7f800000u) return (uint16_t)(s | 0x7e00u);
+    if (u >= 0x477ff000u) return (uint16_t)(s | 0x7c00u);       // rounds to 2^16 or more
+    if (u < 0x38800000u) {                                       // below 2^-14: units of 2^-24
+        float a;
+        std::memcpy(&a, &u, 4);
+        return (uint16_t)(s | (uint32_t)std::nearbyint(a * 16777216.0f));
+    }
+    u += 0xfffu + ((u >> 13) & 1u);
+    return (uint16_t)(s | ((u - 0x38000000u) >> 13));
+}
+
+// The value of f16 bits (finite or infinite).
+inline float f16_value_of(uint16_t h) {
+    const int e = (h >> 10) & 31, m = h & 0x3ff;
+    const float a = e == 31 ? INFINITY : (e ? std::ldexp((float)(m + 1024), e - 25) : std::ldexp((float)m, -24));
+    return h & 0x8000 ? -a : a;
 }
 
 // The same for bf16 operands, k-blocks of 32: lane l holds

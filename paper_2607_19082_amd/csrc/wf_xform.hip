@@ -9,7 +9,7 @@
 //   g_s: 3 x (transposed conv 5x5 s2, inverse GDN) (M -> N -> N -> N), then
 //        transposed conv 5x5 s2 (N -> 3)
 //
-// Every layer is one implicit-GEMM kernel on MFMA.  A stride-2 transposed
+// Every layer is an implicit GEMM on MFMA: k_conv for h_s, k_synth for g_s.  A stride-2 transposed
 // conv (padding 2, output padding 1) splits into four output parity classes
 // (oy mod 2, ox mod 2); class (py, px) is an ordinary product over the taps
 // ky = py + 2 ty, kx = px + 2 tx, reading input pixel (qy + 1 - ty, qx + 1 - tx)
@@ -180,13 +180,383 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
     }
 }
 
+// ---- the synthesis transform's layers ----------------------------------------
+//
+// Bound by the matrix cores (1554 GFLOP at 4K).  fp32 MFMA peaks at 157
+// TFLOP/s, f16 MFMA at sixteen times that, so the fp32 transform runs on f16
+// pairs: x = x0 + x1 with x0 = f16(x), x1 = f16(x - x0) holds 22-23 of fp32's
+// 24 bits, and three products x0 w0 + x0 w1 + x1 w0 accumulate in fp32.  The
+// chain has one rounding per 32 values of k and product where the fp32 MFMA
+// chain has eight, and the sum ends up closer to the 64-bit result than with
+// fp32 operands (4K image: 2.3e-6 relative before).  f16's range is met by
+// scaling with powers of two (exact): each weight column by its largest
+// weight at plan time, the activations by the largest of the workgroup's own
+// patch, found while it is staged (a later chunk with a larger value rescales
+// the accumulators), both to [2^13, 2^14).  A scaled pair is exact to 2^-38 of
+// the patch's largest value, so a workgroup goes to fp32 MFMA on the unscaled
+// inputs (conv_tile_f32) when some pixel's own largest value is below 2^-15 of
+// that (an outlier beside small values; inverse GDN: unless beta covers the
+// difference), and when a value is infinite or NaN, which then propagates as
+// in a product of fp32 values.
+// The bf16 variant (bf16 weights, bf16-pair activations) has two products per
+// operand pair and needs no scaling.
+//
+// A workgroup owns TW x TH output pixels of one parity class and 16 CT WC
+// output channels.  Per chunk of 32 input channels it stages the pixels'
+// patch (halo of one) once, split, in LDS ([half][k-group][pixel] of 16-byte
+// operands: the 16 lanes of a k-group read 256 contiguous bytes), and every
+// tap of the class then reads it shifted.  Weights come straight from L2 in
+// operand order, one tap ahead of their use; a wave holds RT x CT tiles, so
+// each weight operand feeds RT MFMA chains and each activation operand CT.
+// Weights are the first MFMA operand: a lane then holds four consecutive
+// channels of one pixel and stores 16 bytes.  4K (N = 192, M = 320): 20.36 ms
+// with per-wave operand loads and fp32 MFMA, 5.60 ms now (the third
+// transposed conv 13.0 -> 2.95 ms, 325 TFLOP/s of fp32 products); bf16 at
+// 120x68 latents (N = 128): 1.98 -> 0.66 ms.
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+struct SynthArgs {
+    const float* in;
+    float* out;
+    const void* wp[4];        // packed panel per output class: [Cop/16][chunk][tap][NW][64] operands
+    const int* ce;            // f16: [Cop] exponent each weight column was scaled by
+    const float* bias;        // [Cop] bias (GDN: beta), zero-padded
+    int B, Hi, Wi, Ci;        // input [B][Hi][Wi][Ci] (GDN: one row of all pixels)
+    int Co, Cop, nch;         // output channels, padded; chunks of 32 input channels
+    int Ho, Wo;               // output pixels
+    int twl, ntx, nty;        // log2 of the tile's width; tiles along x, y
+    int ncb, ncls;            // column blocks, classes
+    int force_f32;            // a weight is not finite
+    float covered;            // GDN: largest x^2 whose scaled error beta covers in every channel
+};
+
+constexpr int kSynthMinBlocks = 256;
+
+struct SF16 {                 // fp32 transform on f16 pairs
+    using V = h8;
+    static constexpr int kNw = 2;
+    static constexpr bool kScaled = true;
+};
+struct SBF16 {                // bf16 transform: bf16 weights, bf16-pair activations
+    using V = b8;
+    static constexpr int kNw = 1;
+    static constexpr bool kScaled = false;
+};
+
+__device__ __forceinline__ f4 mfma_k32(h8 a, h8 b, f4 acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mfma_k32(b8 a, b8 b, f4 acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+
+// Largest |x| of a workgroup's threads as fp32 bits (an infinity or NaN then
+// exceeds every finite value).  Holds a barrier.
+__device__ __forceinline__ unsigned block_max_bits(unsigned m, unsigned* red) {
+#pragma unroll
+    for (int o = 32; o; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(max(max(red[0], red[1]), max(red[2], red[3])));
+}
+__device__ __forceinline__ unsigned abs_bits(float v) { return __builtin_bit_cast(unsigned, v) & 0x7fffffffu; }
+constexpr unsigned kInfBits = 0x7f800000u;
+constexpr int kSynthRange = 15;   // binary orders a pixel's largest value may lie below its patch's
+// Exponent that scales a largest value with these bits to [2^13, 2^14).
+__device__ __forceinline__ int scale_exp(unsigned bits) { return 127 + 13 - (int)(bits >> 23); }
+
+// f16 pair of eight values scaled by 2^s.
+__device__ __forceinline__ void split_f16(const float (&x)[8], int s, h8& hi, h8& lo) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const float v = ldexpf(x[q], s);
+        hi[q] = (_Float16)v;
+        lo[q] = (_Float16)(v - (float)hi[q]);
+    }
+}
+
+template <int MODE, int RT, int CT, int WC>
+struct SynthShape {
+    static constexpr int kWr = 4 / WC;                         // waves along the pixels
+    static constexpr int kPx = 16 * RT * kWr;                  // pixels of a workgroup
+    static constexpr int kCols = 16 * CT * WC;                 // output channels of a workgroup
+    static constexpr int kHalo = MODE == XM_GDN ? 0 : 1;
+    // patch pixels: 128 as 16 x 8 or 8 x 16, 64 as 16 x 4 or 8 x 8
+    static constexpr int kPatch = !kHalo ? kPx : (kPx == 128 ? 180 : 108);
+    static constexpr int kItems = (kPatch * 4 + kThreads - 1) / kThreads;
+};
+
+// The tile in fp32 arithmetic, from the unscaled inputs and the weights put
+// back together: the path of inputs that are not finite.
+template <int MODE, int RT, int CT>
+__device__ __forceinline__ void conv_tile_f32(const SynthArgs& a, const void* wp, int nk, int ntap, int nkx, int b, const int (&qy)[RT],
+                              const int (&qx)[RT], int ct0, f4 (&acc)[RT][CT]) {
+    const int lane = threadIdx.x & 63, kq = lane >> 4;
+    const h8* w = static_cast<const h8*>(wp) + lane;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = zero4();
+    for (int k = 0; k < nk; ++k) {
+        const int ch = k / ntap, t = k - ch * ntap, ty = t / nkx, tx = t - ty * nkx;
+        const int dy = MODE == XM_DECONV ? 1 - ty : (MODE == XM_GDN ? 0 : ty - 1);
+        const int dx = MODE == XM_DECONV ? 1 - tx : (MODE == XM_GDN ? 0 : tx - 1);
+        const int c = ch * 32 + kq * 8;
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int n = (ct0 + j) * kTile + (lane & 15);
+            const bool cv = (ct0 + j) * kTile < a.Cop;
+            const h8* p = w + ((size_t)(cv ? ct0 + j : 0) * nk + k) * 2 * 64;
+            const h8 w0 = p[0], w1 = p[64];
+            const int e = cv ? -a.ce[n] : 0;
+            float wf[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) wf[q] = ldexpf((float)w0[q] + (float)w1[q], e);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const int iy = qy[i] + dy, ix = qx[i] + dx;
+                const bool ok = iy >= 0 && iy < a.Hi && ix >= 0 && ix < a.Wi && c < a.Ci;
+                const size_t q0 = (((size_t)b * a.Hi + iy) * a.Wi + ix) * a.Ci + c;
+                const f4 u = ld4<false>(a.in, q0, ok), v = ld4<false>(a.in, q0 + 4, ok);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    float x = q < 4 ? u[q & 3] : v[q & 3];
+                    if (MODE == XM_GDN) x = x * x;
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[q], x, acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+template <class P, int MODE, int RT, int CT, int WC>
+__global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
+    using V = typename P::V;
+    using S = SynthShape<MODE, RT, CT, WC>;
+    constexpr int NW = P::kNw, NI = S::kItems, NP = S::kPatch, HALO = S::kHalo;
+    __shared__ V patch[2][4][NP];                        // [hi, lo][k-group][pixel]
+    __shared__ unsigned red[4];
+
+    // consecutive work on one XCD: the classes and column blocks of a tile,
+    // and neighbouring tiles, share patches in its L2
+    const int per = gridDim.x / kXcds;
+    int id = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    if (id >= a.B * a.nty * a.ntx * a.ncls * a.ncb) return;
+    const int cb = id % a.ncb;
+    id /= a.ncb;
+    const int cls = id % a.ncls, py = cls >> 1, px = cls & 1;
+    id /= a.ncls;
+    const int tx = id % a.ntx;
+    id /= a.ntx;
+    const int ty = id % a.nty, b = id / a.nty;
+    const int TW = 1 << a.twl, TH = S::kPx >> a.twl, PW = TW + 2 * HALO, np = PW * (TH + 2 * HALO);
+    const int y0 = ty * TH, x0 = tx * TW;
+
+    const int nkx = MODE == XM_DECONV ? (px ? 2 : 3) : (MODE == XM_GDN ? 1 : 3);
+    const int nky = MODE == XM_DECONV ? (py ? 2 : 3) : (MODE == XM_GDN ? 1 : 3);
+    const int ntap = nkx * nky, nk = a.nch * ntap;
+
+    const int wave = wave_id(), lane = threadIdx.x & 63, kq = lane >> 4;
+    const int wr = wave / WC, wc = wave % WC;
+    const int ct0 = (cb * WC + wc) * CT, nct = a.Cop / kTile;
+
+    // patch items of this thread: pixel e / 4, channels 8 (e % 4) .. + 8
+    int src[NI];
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+        const int e = threadIdx.x + n * kThreads, p = e >> 2;
+        const int ry = p / PW, iy = y0 - HALO + ry, ix = x0 - HALO + (p - ry * PW);
+        const bool ok = p < np && iy >= 0 && iy < a.Hi && ix >= 0 && ix < a.Wi;
+        src[n] = ok ? (int)((((size_t)b * a.Hi + iy) * a.Wi + ix) * a.Ci + (e & 3) * 8) : -1;
+    }
+    float st[NI][8];
+    auto load_chunk = [&](int ch) {
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const bool ok = src[n] >= 0 && ch * 32 + (threadIdx.x & 3) * 8 < a.Ci;
+            const f4 u = ld4<false>(a.in, (size_t)(src[n] + ch * 32), ok), v = ld4<false>(a.in, (size_t)(src[n] + ch * 32 + 4), ok);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                st[n][q] = MODE == XM_GDN ? u[q] * u[q] : u[q];
+                st[n][4 + q] = MODE == XM_GDN ? v[q] * v[q] : v[q];
+            }
+        }
+    };
+
+    // weights of k-step k: column tile ct at w + (ct nk + k) NW 64
+    const V* w = static_cast<const V*>(a.wp[cls]) + lane;
+    size_t wo[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) wo[j] = (size_t)(ct0 + j < nct ? ct0 + j : 0) * nk * NW * 64;
+    auto load_w = [&](int k, V (&wv)[CT][NW]) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int n = 0; n < NW; ++n) wv[j][n] = w[wo[j] + (size_t)(k * NW + n) * 64];
+    };
+
+    // this lane's pixel of row tile i: patch index of its tap (0, 0), and the
+    // step from one row tile to the next
+    const int r0 = wr * RT * kTile + (lane & 15);
+    const int at0 = kq * NP + (r0 >> a.twl) * PW + (r0 & (TW - 1));
+    const int step = MODE == XM_GDN ? kTile : (kTile >> a.twl) * PW;
+    const V* lds = &patch[0][0][0];
+
+    f4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = zero4();
+
+    int s = 1000;                                        // the activations' scale exponent (1000: none yet)
+    unsigned big = 0, pm[NI];                            // largest |x| (bits) of the patch and of this thread's items
+#pragma unroll
+    for (int n = 0; n < NI; ++n) pm[n] = 0;
+    bool bad = P::kScaled && a.force_f32;
+    V wv[CT][NW], wn[CT][NW];
+    load_chunk(0);
+    load_w(0, wv);
+    for (int ch = 0; ch < a.nch && !bad; ++ch) {
+        if constexpr (P::kScaled) {
+            unsigned m = 0;
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) pm[n] = max(pm[n], abs_bits(st[n][q]));
+                m = max(m, pm[n]);
+            }
+            m = block_max_bits(m, red);                  // (its barrier: the chunk before has been read)
+            big = m;
+            if (m >= kInfBits) {
+                bad = true;
+                break;
+            }
+            const int need = scale_exp(m);
+            if (need < s) {
+                if (s < 1000)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+#pragma unroll
+                        for (int j = 0; j < CT; ++j)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) acc[i][j][q] = ldexpf(acc[i][j][q], need - s);
+                s = need;
+            }
+        } else {
+            __syncthreads();
+        }
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int e = threadIdx.x + n * kThreads;
+            if (NP * 4 % kThreads == 0 || e < NP * 4) {
+                V hi, lo;
+                if constexpr (P::kScaled) {
+                    split_f16(st[n], s, hi, lo);
+                } else {
+                    const b8x2 p = split8(f4{st[n][0], st[n][1], st[n][2], st[n][3]}, f4{st[n][4], st[n][5], st[n][6], st[n][7]});
+                    hi = p.hi;
+                    lo = p.lo;
+                }
+                patch[0][e & 3][e >> 2] = hi;
+                patch[1][e & 3][e >> 2] = lo;
+            }
+        }
+        __syncthreads();
+        if (ch + 1 < a.nch) load_chunk(ch + 1);
+        int tap = 0;
+        for (int t0 = 0; t0 < nky; ++t0)
+            for (int t1 = 0; t1 < nkx; ++t1, ++tap) {
+                const int k = ch * ntap + tap;
+                load_w(min(k + 1, nk - 1), wn);
+                // patch row and column of this tap's pixel: dy + 1 and dx + 1
+                const int oy = MODE == XM_DECONV ? 2 - t0 : t0, ox = MODE == XM_DECONV ? 2 - t1 : t1;
+                const int at = at0 + (MODE == XM_GDN ? 0 : oy * PW + ox);
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    const V hi = lds[at + i * step], lo = lds[4 * NP + at + i * step];
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) acc[i][j] = mfma_k32(wv[j][0], hi, acc[i][j]);
+                    if constexpr (NW == 2) {
+#pragma unroll
+                        for (int j = 0; j < CT; ++j) acc[i][j] = mfma_k32(wv[j][1], hi, acc[i][j]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) acc[i][j] = mfma_k32(wv[j][0], lo, acc[i][j]);
+                }
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+#pragma unroll
+                    for (int n = 0; n < NW; ++n) wv[j][n] = wn[j][n];
+            }
+    }
+
+    int qy[RT], qx[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int r = r0 + i * kTile;
+        qy[i] = y0 + (r >> a.twl);
+        qx[i] = x0 + (r & (TW - 1));
+    }
+    if constexpr (P::kScaled) {
+        if (!bad && big > kSynthRange << 23 && (MODE != XM_GDN || big > __builtin_bit_cast(unsigned, a.covered))) {
+            int low = 0;
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {               // the four lanes of a pixel hold its k-groups
+                unsigned m = max(pm[n], (unsigned)__shfl_xor((int)pm[n], 1));
+                m = max(m, (unsigned)__shfl_xor((int)m, 2));
+                low |= m != 0 && m < big - (kSynthRange << 23);
+            }
+            bad = __syncthreads_or(low);
+        }
+        if (bad) {
+            s = 0;
+            conv_tile_f32<MODE, RT, CT>(a, a.wp[cls], nk, ntap, nkx, b, qy, qx, ct0, acc);
+        }
+    }
+    // a lane holds channels 4 (lane / 16) + q of each column tile, pixel lane % 16
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+        const int n = (ct0 + j) * kTile + kq * 4;
+        if (ct0 + j >= nct) continue;
+        const f4 add = *reinterpret_cast<const f4*>(a.bias + n);
+        int4 e{0, 0, 0, 0};
+        if (P::kScaled && !bad) e = *reinterpret_cast<const int4*>(a.ce + n);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (qy[i] >= a.Hi || qx[i] >= a.Wi) continue;
+            f4 v = acc[i][j];
+            if constexpr (P::kScaled)
+                if (!bad) v = f4{ldexpf(v.x, -s - e.x), ldexpf(v.y, -s - e.y), ldexpf(v.z, -s - e.z), ldexpf(v.w, -s - e.w)};
+            v = v + add;
+            if (MODE == XM_DECONV4) {                    // columns (class, channel)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c4 = (n + q) / a.Co, c = n + q - c4 * a.Co;
+                    if (c4 < 4)
+                        a.out[(((size_t)b * a.Ho + 2 * qy[i] + (c4 >> 1)) * a.Wo + 2 * qx[i] + (c4 & 1)) * a.Co + c] = v[q];
+                }
+            } else {
+                const int oy = MODE == XM_DECONV ? 2 * qy[i] + py : qy[i], ox = MODE == XM_DECONV ? 2 * qx[i] + px : qx[i];
+                const size_t o = (((size_t)b * a.Ho + oy) * a.Wo + ox) * a.Co + n;
+                if (MODE == XM_GDN) {
+                    const f4 x = *reinterpret_cast<const f4*>(a.in + o);
+                    v = f4{x.x * sqrtf(v.x), x.y * sqrtf(v.y), x.z * sqrtf(v.z), x.w * sqrtf(v.w)};
+                }
+                *reinterpret_cast<f4*>(a.out + o) = v;
+            }
+        }
+    }
+}
+
 // ---- plan -------------------------------------------------------------------
 
 struct Layer {
     int mode, Ci, Co, Cop, relu;
     const void* wp[4];
-    const float* bias;
-    const float* beta;
+    const float* bias;        // h_s: [Co]; g_s: [Cop] (GDN: beta)
+    const int* ce;            // g_s, fp32: [Cop] scale exponents of the weight columns
+    int force_f32;            // g_s, fp32: a weight is not finite
+    float covered;            // inverse GDN, fp32: see SynthArgs
 };
 
 struct Xform {
@@ -225,46 +595,110 @@ template <class F>
 static int xf_pack(Xform* x, Layer& L, int nclass, F wt) {
     const bool bf = x->precision == WF_BF16;
     for (int c = 0; c < nclass; ++c) {
-        const int py = c >> 1, px = c & 1;
-        const int nky = L.mode == XM_DECONV ? (py ? 2 : 3) : (L.mode == XM_GDN ? 1 : 3);
-        const int nkx = L.mode == XM_DECONV ? (px ? 2 : 3) : (L.mode == XM_GDN ? 1 : 3);
+        const int nky = L.mode == XM_DECONV && (c >> 1) ? 2 : 3, nkx = L.mode == XM_DECONV && (c & 1) ? 2 : 3;
         const int K = nky * nkx * L.Ci;
         auto f = [&](int k, int n) { return wt(c, k / L.Ci, nkx, k % L.Ci, n); };
-        const int ncol = L.mode == XM_DECONV4 ? 4 * L.Co : L.Co;   // columns that carry weights
-        int rc = bf ? xf_upload(x, reinterpret_cast<const uint16_t**>(&L.wp[c]), pack_panel_bf16(K, ncol, K, L.Cop, f))
-                    : xf_upload(x, reinterpret_cast<const float**>(&L.wp[c]), pack_panel(K, ncol, K, L.Cop, f));
+        int rc = bf ? xf_upload(x, reinterpret_cast<const uint16_t**>(&L.wp[c]), pack_panel_bf16(K, L.Co, K, L.Cop, f))
+                    : xf_upload(x, reinterpret_cast<const float**>(&L.wp[c]), pack_panel(K, L.Co, K, L.Cop, f));
         if (rc != WF_OK) return rc;
     }
     for (int c = nclass; c < 4; ++c) L.wp[c] = L.wp[0];
     return WF_OK;
 }
 
+// Pack one layer of g_s for k_synth: wt(c, t, nkx, ci, n) as above over ncol
+// columns, k in (chunk of 32 input channels, tap, channel) order, and the
+// bias (or beta) of every column.
+template <class F, class G>
+static int xf_pack_synth(Xform* x, Layer& L, int nclass, int ncol, F wt, G bias) {
+    const bool bf = x->precision == WF_BF16;
+    const int nch = (L.Ci + 31) / 32, nw = bf ? 1 : 2;
+    auto taps = [&](int c, int& nkx) {
+        nkx = L.mode == XM_GDN ? 1 : (L.mode == XM_DECONV && (c & 1) ? 2 : 3);
+        return nkx * (L.mode == XM_GDN ? 1 : (L.mode == XM_DECONV && (c >> 1) ? 2 : 3));
+    };
+    std::vector<int> ce(L.Cop, 0);
+    L.force_f32 = 0;
+    if (!bf)
+        for (int n = 0; n < ncol; ++n) {
+            float big = 0.0f;
+            for (int c = 0; c < nclass; ++c) {
+                int nkx;
+                const int nt = taps(c, nkx);
+                for (int t = 0; t < nt; ++t)
+                    for (int ci = 0; ci < L.Ci; ++ci) {
+                        const float v = fabsf(wt(c, t, nkx, ci, n));
+                        if (!std::isfinite(v)) L.force_f32 = 1;
+                        else if (v > big) big = v;
+                    }
+            }
+            if (big > 0.0f) ce[n] = 13 - std::ilogb(big);   // the largest to [2^13, 2^14)
+        }
+    for (int c = 0; c < nclass; ++c) {
+        int nkx;
+        const int nt = taps(c, nkx), nk = nch * nt;
+        std::vector<uint16_t> v((size_t)L.Cop / kTile * nk * nw * 64 * 8, 0);
+        for (int n = 0; n < ncol; ++n)
+            for (int k = 0; k < nk; ++k)
+                for (int q = 0; q < 32; ++q) {
+                    const int ci = k / nt * 32 + q;
+                    if (ci >= L.Ci) continue;
+                    const float f = wt(c, k % nt, nkx, ci, n);
+                    const size_t at = (((size_t)(n / kTile) * nk + k) * nw * 64 + (q / 8) * 16 + n % kTile) * 8 + q % 8;
+                    if (bf) {
+                        v[at] = bf16_round(f);
+                    } else {
+                        const float g = std::ldexp(f, ce[n]);
+                        const uint16_t h = f16_round(g);
+                        v[at] = h;
+                        v[at + 64 * 8] = std::isfinite(g) ? f16_round(g - f16_value_of(h)) : 0;
+                    }
+                }
+        int rc = xf_upload(x, reinterpret_cast<const uint16_t**>(&L.wp[c]), v);
+        if (rc != WF_OK) return rc;
+    }
+    for (int c = nclass; c < 4; ++c) L.wp[c] = L.wp[0];
+    std::vector<float> bv(L.Cop, 0.0f);
+    for (int n = 0; n < ncol; ++n) bv[n] = bias(n);
+    int rc = xf_upload(x, &L.bias, bv);
+    return rc != WF_OK ? rc : xf_upload(x, &L.ce, ce);
+}
+
 // Transposed conv weight W[ci][co][5][5]: tap t of class (py, px) is
 // (ky, kx) = (py + 2 (t / nkx), px + 2 (t % nkx)).
+static float deconv_w(const float* w, int Co, int c, int t, int nkx, int ci, int co) {
+    const int ky = (c >> 1) + 2 * (t / nkx), kx = (c & 1) + 2 * (t % nkx);
+    return w[(((size_t)ci * Co + co) * 5 + ky) * 5 + kx];
+}
+
 static int xf_deconv(Xform* x, Layer& L, const float* w, const float* b, int Ci, int Co, int relu) {
     L.mode = XM_DECONV; L.Ci = Ci; L.Co = Co; L.Cop = (Co + kTile - 1) / kTile * kTile; L.relu = relu;
-    int rc = xf_pack(x, L, 4, [&](int c, int t, int nkx, int ci, int co) {
-        const int ky = (c >> 1) + 2 * (t / nkx), kx = (c & 1) + 2 * (t % nkx);
-        return w[(((size_t)ci * Co + co) * 5 + ky) * 5 + kx];
-    });
+    int rc = xf_pack(x, L, 4, [&](int c, int t, int nkx, int ci, int co) { return deconv_w(w, Co, c, t, nkx, ci, co); });
     if (rc != WF_OK) return rc;
     return xf_upload(x, &L.bias, std::vector<float>(b, b + Co));
+}
+
+static int xf_synth_deconv(Xform* x, Layer& L, const float* w, const float* b, int Ci, int Co) {
+    L.mode = XM_DECONV; L.Ci = Ci; L.Co = Co; L.Cop = (Co + kTile - 1) / kTile * kTile; L.relu = 0;
+    return xf_pack_synth(x, L, 4, Co,
+        [&](int c, int t, int nkx, int ci, int co) { return deconv_w(w, Co, c, t, nkx, ci, co); },
+        [&](int n) { return b[n]; });
 }
 
 // All four classes in the columns (Co <= 4): column n = class * Co + co, tap
 // (dy, dx) = (t / 3 - 1, t % 3 - 1) of the input neighbourhood, which class
 // (py, px) reaches through (ky, kx) = (py + 2 - 2 dy, px + 2 - 2 dx) when both
 // are at most 4 (zero weight otherwise).
-static int xf_deconv4(Xform* x, Layer& L, const float* w, const float* b, int Ci, int Co) {
+static int xf_synth_deconv4(Xform* x, Layer& L, const float* w, const float* b, int Ci, int Co) {
     L.mode = XM_DECONV4; L.Ci = Ci; L.Co = Co; L.Cop = (4 * Co + kTile - 1) / kTile * kTile; L.relu = 0;
-    int rc = xf_pack(x, L, 1, [&](int, int t, int, int ci, int n) -> float {
-        const int cls = n / Co, co = n - cls * Co;
-        const int ky = (cls >> 1) + 2 - 2 * (t / 3 - 1), kx = (cls & 1) + 2 - 2 * (t % 3 - 1);
-        if (ky > 4 || kx > 4) return 0.0f;
-        return w[(((size_t)ci * Co + co) * 5 + ky) * 5 + kx];
-    });
-    if (rc != WF_OK) return rc;
-    return xf_upload(x, &L.bias, std::vector<float>(b, b + Co));
+    return xf_pack_synth(x, L, 1, 4 * Co,
+        [&](int, int t, int, int ci, int n) -> float {
+            const int cls = n / Co, co = n - cls * Co;
+            const int ky = (cls >> 1) + 2 - 2 * (t / 3 - 1), kx = (cls & 1) + 2 - 2 * (t % 3 - 1);
+            if (ky > 4 || kx > 4) return 0.0f;
+            return w[(((size_t)ci * Co + co) * 5 + ky) * 5 + kx];
+        },
+        [&](int n) { return b[n % Co]; });
 }
 
 static int xf_conv3(Xform* x, Layer& L, const float* w, const float* b, int Ci, int Co) {
@@ -276,18 +710,26 @@ static int xf_conv3(Xform* x, Layer& L, const float* w, const float* b, int Ci, 
     return xf_upload(x, &L.bias, std::vector<float>(b, b + Co));
 }
 
-static int xf_gdn(Xform* x, Layer& L, const float* beta, const float* gamma, int C) {
+static int xf_synth_gdn(Xform* x, Layer& L, const float* beta, const float* gamma, int C) {
+    // an error of 2^-38 of the patch's largest square in each of them adds at
+    // most 2^-38 max sum_j gamma_cj to z_c; 2^-23 beta_c or less counts as covered
+    double cov = 3e38;
+    for (int c = 0; c < C; ++c) {
+        double sum = 0.0;
+        for (int j = 0; j < C; ++j) sum += std::fabs((double)gamma[(size_t)c * C + j]);
+        cov = std::fmin(cov, 32768.0 * std::fabs((double)beta[c]) / sum);
+    }
+    L.covered = cov > 0.0 ? (float)cov : 0.0f;
     L.mode = XM_GDN; L.Ci = C; L.Co = C; L.Cop = (C + kTile - 1) / kTile * kTile; L.relu = 0;
-    int rc = xf_pack(x, L, 1, [&](int, int, int, int j, int c) { return gamma[(size_t)c * C + j]; });
-    if (rc != WF_OK) return rc;
-    return xf_upload(x, &L.beta, std::vector<float>(beta, beta + C));
+    return xf_pack_synth(x, L, 1, C, [&](int, int, int, int j, int c) { return gamma[(size_t)c * C + j]; },
+                         [&](int n) { return beta[n]; });
 }
 
 template <class P, int MODE>
 static void launch_layer(const Layer& L, const float* in, float* out, int B, int Hi, int Wi, int Hq, int Wq, int Ho,
                          int Wo, hipStream_t st) {
     ConvArgs a{};
-    a.in = in; a.out = out; a.bias = L.bias; a.beta = L.beta;
+    a.in = in; a.out = out; a.bias = L.bias;
     for (int c = 0; c < 4; ++c) a.wp[c] = L.wp[c];
     a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ci = L.Ci; a.Hq = Hq; a.Wq = Wq;
     a.Co = L.Co; a.Cop = L.Cop; a.Ho = Ho; a.Wo = Wo; a.relu = L.relu;
@@ -297,25 +739,72 @@ static void launch_layer(const Layer& L, const float* in, float* out, int B, int
     // already hold twice the registers per operand and keep 2 (measured:
     // 4 was 5% slower there).
     constexpr int RTW = P::kBf16 ? 2 : 4;
-    if (nct <= 1) {   // narrow output (the image's 3 channels): 4 RTW row tiles x 1 column tile per workgroup
-        using S = ConvShape<RTW, 1, 1>;
-        const int nb = ((nrows + S::kRowTiles * kTile - 1) / (S::kRowTiles * kTile)) * nct;
-        hipLaunchKernelGGL((k_conv<P, MODE, RTW, 1, 1>), dim3(nb, 1, ncls), dim3(kThreads), 0, st, a);
-    } else {          // 2 RTW row tiles x 4 column tiles per workgroup
-        using S = ConvShape<RTW, 2, 2>;
-        const int nb = ((nrows + S::kRowTiles * kTile - 1) / (S::kRowTiles * kTile)) *
-                       ((nct + S::kColTiles - 1) / S::kColTiles);
-        hipLaunchKernelGGL((k_conv<P, MODE, RTW, 2, 2>), dim3(nb, 1, ncls), dim3(kThreads), 0, st, a);
-    }
+    using S = ConvShape<RTW, 2, 2>;      // 2 RTW row tiles x 4 column tiles per workgroup
+    const int nb = ((nrows + S::kRowTiles * kTile - 1) / (S::kRowTiles * kTile)) *
+                   ((nct + S::kColTiles - 1) / S::kColTiles);
+    hipLaunchKernelGGL((k_conv<P, MODE, RTW, 2, 2>), dim3(nb, 1, ncls), dim3(kThreads), 0, st, a);
 }
 
 template <class P>
 static void run_layer(const Layer& L, const float* in, float* out, int B, int Hi, int Wi, int Ho, int Wo,
                       hipStream_t st) {
     if (L.mode == XM_DECONV) launch_layer<P, XM_DECONV>(L, in, out, B, Hi, Wi, Hi, Wi, Ho, Wo, st);
-    else if (L.mode == XM_CONV3) launch_layer<P, XM_CONV3>(L, in, out, B, Hi, Wi, Ho, Wo, Ho, Wo, st);
-    else if (L.mode == XM_DECONV4) launch_layer<P, XM_DECONV4>(L, in, out, B, Hi, Wi, Hi, Wi, Ho, Wo, st);
-    else launch_layer<P, XM_GDN>(L, in, out, B, Hi, Wi, Hi, Wi, Hi, Wi, st);
+    else launch_layer<P, XM_CONV3>(L, in, out, B, Hi, Wi, Ho, Wo, Ho, Wo, st);
+}
+
+static int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Tiles of a launch: along x and y, for a tile 2^twl wide.
+template <class S>
+static int synth_tiles(SynthArgs& a, int twl) {
+    const int tw = 1 << twl, th = S::kPx >> twl;
+    a.twl = twl;
+    a.ntx = ceil_div(a.Wi, tw);
+    a.nty = ceil_div(a.Hi, th);
+    return a.ntx * a.nty;
+}
+
+template <class P, int MODE, int RT, int CT, int WC>
+static void launch_synth(SynthArgs a, hipStream_t st) {
+    using S = SynthShape<MODE, RT, CT, WC>;
+    if (!S::kHalo) synth_tiles<S>(a, S::kPx == 128 ? 7 : 6);
+    else if (synth_tiles<S>(a, 3) >= synth_tiles<S>(a, 4)) synth_tiles<S>(a, 4);   // the shape that pads less
+    else synth_tiles<S>(a, 3);
+    a.ncb = ceil_div(a.Cop, S::kCols);
+    const int n = a.B * a.nty * a.ntx * a.ncls * a.ncb;
+    hipLaunchKernelGGL((k_synth<P, MODE, RT, CT, WC>), dim3(ceil_div(n, kXcds) * kXcds), dim3(kThreads), 0, st, a);
+}
+
+template <class P, int MODE>
+static void run_synth_mode(const SynthArgs& a, hipStream_t st) {
+    const long long px = (long long)a.B * a.Hi * a.Wi * a.ncls;
+    // 128 pixels x 192 or 128 channels, whichever pads fewer columns, unless
+    // that leaves compute units without a workgroup: then 64 x 64.
+    const int n3 = ceil_div(a.Cop, 192), n2 = ceil_div(a.Cop, 128);
+    const bool wide = n3 * 192 <= n2 * 128;
+    if (px / 128 * (wide ? n3 : n2) < kSynthMinBlocks) launch_synth<P, MODE, 4, 1, 4>(a, st);
+    else if (wide) launch_synth<P, MODE, 8, 3, 4>(a, st);
+    else launch_synth<P, MODE, 8, 2, 4>(a, st);
+}
+
+// One layer of g_s: [B][h][w][Ci] -> [B][2h][2w][Co] (GDN: the same grid).
+template <class P>
+static void run_synth(const Layer& L, const float* in, float* out, int B, int h, int w, hipStream_t st) {
+    SynthArgs a{};
+    a.in = in; a.out = out; a.bias = L.bias; a.ce = L.ce; a.force_f32 = L.force_f32; a.covered = L.covered;
+    for (int c = 0; c < 4; ++c) a.wp[c] = L.wp[c];
+    a.Ci = L.Ci; a.Co = L.Co; a.Cop = L.Cop; a.nch = ceil_div(L.Ci, 32);
+    a.B = B; a.Hi = h; a.Wi = w; a.Ho = 2 * h; a.Wo = 2 * w; a.ncls = 1;
+    if (L.mode == XM_DECONV) {
+        a.ncls = 4;
+        run_synth_mode<P, XM_DECONV>(a, st);
+    } else if (L.mode == XM_GDN) {
+        a.B = a.Hi = a.Ho = 1;
+        a.Wi = a.Wo = B * h * w;
+        run_synth_mode<P, XM_GDN>(a, st);
+    } else {
+        launch_synth<P, XM_DECONV4, 2, 1, 1>(a, st);
+    }
 }
 
 template <class P>
@@ -328,17 +817,16 @@ static void hyper(const Xform& x, const float* z, float* psi, hipStream_t st) {
 
 template <class P>
 static void synth(const Xform& x, const float* y, float* img, hipStream_t st) {
-    const int B = x.B;
     int h = x.H, w = x.W;
     const float* in = y;
     for (int k = 0; k < 3; ++k) {
-        run_layer<P>(x.gs[k], in, x.g_a, B, h, w, 2 * h, 2 * w, st);
+        run_synth<P>(x.gs[k], in, x.g_a, x.B, h, w, st);
         h *= 2;
         w *= 2;
-        run_layer<P>(x.gdn[k], x.g_a, x.g_b, B, h, w, h, w, st);
+        run_synth<P>(x.gdn[k], x.g_a, x.g_b, x.B, h, w, st);
         in = x.g_b;
     }
-    run_layer<P>(x.gs[3], in, img, B, h, w, 2 * h, 2 * w, st);
+    run_synth<P>(x.gs[3], in, img, x.B, h, w, st);
 }
 
 static void free_xform(Xform* x) {
@@ -386,9 +874,9 @@ int wf_xform_plan(const wf_xform_desc* d, wf_xform_t* out) {
     if (rc == WF_OK) rc = xf_conv3(x, x->hs[2], d->hs_w[2], d->hs_b[2], C, 2 * M);
     const int gi[4] = {M, N, N, N}, go[4] = {N, N, N, 3};
     for (int k = 0; k < 4 && rc == WF_OK; ++k) {
-        rc = go[k] <= 4 ? xf_deconv4(x, x->gs[k], d->gs_w[k], d->gs_b[k], gi[k], go[k])
-                        : xf_deconv(x, x->gs[k], d->gs_w[k], d->gs_b[k], gi[k], go[k], 0);
-        if (rc == WF_OK && k < 3) rc = xf_gdn(x, x->gdn[k], d->gdn_beta[k], d->gdn_gamma[k], N);
+        rc = go[k] <= 4 ? xf_synth_deconv4(x, x->gs[k], d->gs_w[k], d->gs_b[k], gi[k], go[k])
+                        : xf_synth_deconv(x, x->gs[k], d->gs_w[k], d->gs_b[k], gi[k], go[k]);
+        if (rc == WF_OK && k < 3) rc = xf_synth_gdn(x, x->gdn[k], d->gdn_beta[k], d->gdn_gamma[k], N);
     }
     const size_t B = d->B;
     if (rc == WF_OK) rc = xf_alloc(x, &x->hs_a, B * 2 * x->Hz * 2 * x->Wz * M);
@@ -415,8 +903,8 @@ int wf_hyper_synthesis(wf_xform_t plan, const float* z_hat, float* psi, hipStrea
 int wf_synthesis(wf_xform_t plan, const float* y_hat, float* image, hipStream_t stream) {
     if (!plan || !y_hat || !image) return fail(WF_E_INVALID, "plan, y_hat or image is NULL");
     const Xform& x = *reinterpret_cast<Xform*>(plan);
-    if (x.precision == WF_BF16) synth<PBF16>(x, y_hat, image, stream);
-    else synth<PF32>(x, y_hat, image, stream);
+    if (x.precision == WF_BF16) synth<SBF16>(x, y_hat, image, stream);
+    else synth<SF16>(x, y_hat, image, stream);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? WF_OK : xf_fail_hip(e, "transform launch");
 }
