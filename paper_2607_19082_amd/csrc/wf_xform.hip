@@ -24,6 +24,7 @@
 // neighbourhood (taps a class does not use have zero weights), so one
 // 16-column tile carries all 12 outputs of an input pixel.
 #include <cmath>
+#include <utility>
 #include <vector>
 
 #include "wf_device.h"
@@ -210,9 +211,10 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
 // each weight operand feeds RT MFMA chains and each activation operand CT.
 // Weights are the first MFMA operand: a lane then holds four consecutive
 // channels of one pixel and stores 16 bytes.  4K (N = 192, M = 320): 20.36 ms
-// with per-wave operand loads and fp32 MFMA, 5.60 ms now (the third
-// transposed conv 13.0 -> 2.95 ms, 325 TFLOP/s of fp32 products); bf16 at
-// 120x68 latents (N = 128): 1.98 -> 0.66 ms.
+// with per-wave operand loads and fp32 MFMA, 4.95 ms now (the third layer
+// with its inverse GDN 3.2 ms, 345 TFLOP/s of fp32 products, the matrix cores
+// busy 57% at the 1.7 GHz that they then draw); bf16 at 120x68 latents
+// (N = 128): 1.98 -> 0.44 ms.
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 struct SynthArgs {
@@ -228,9 +230,18 @@ struct SynthArgs {
     int ncb, ncls;            // column blocks, classes
     int force_f32;            // a weight is not finite
     float covered;            // GDN: largest x^2 whose scaled error beta covers in every channel
+    // inverse GDN in the epilogue of a transposed conv (k_synth with FUSE):
+    const void* gwp;          // packed gamma^T [Cop/16][chunk][NW][64]
+    const int* gce;           // f16: [Cop] scale exponents
+    const float* beta;        // [Cop]
+    int gforce;               // a gamma is not finite
 };
 
+// Workgroups of 128 pixels from which they are the faster ones (fp32, whole
+// transform of a 16x16 latent, whose third layer has 128 of them: 119 us, with
+// 64 x 64 tiles there 107; 50x75, second layer 469: 329 and 340).
 constexpr int kSynthMinBlocks = 256;
+constexpr int kSynthGroup = 32;   // tiles of a group (see k_synth)
 
 struct SF16 {                 // fp32 transform on f16 pairs
     using V = h8;
@@ -281,16 +292,18 @@ struct SynthShape {
     static constexpr int kPx = 16 * RT * kWr;                  // pixels of a workgroup
     static constexpr int kCols = 16 * CT * WC;                 // output channels of a workgroup
     static constexpr int kHalo = MODE == XM_GDN ? 0 : 1;
-    // patch pixels: 128 as 16 x 8 or 8 x 16, 64 as 16 x 4 or 8 x 8
-    static constexpr int kPatch = !kHalo ? kPx : (kPx == 128 ? 180 : 108);
+    // patch pixels: 128 as 16 x 8 or 8 x 16 (180 with the halo), 64 as 16 x 4
+    // or 8 x 8 (108), rounded up to 16: the k-groups' planes then start 256
+    // bytes apart, and the lanes that one LDS cycle serves hit distinct banks
+    static constexpr int kPatch = !kHalo ? kPx : (kPx == 128 ? 192 : 112);
     static constexpr int kItems = (kPatch * 4 + kThreads - 1) / kThreads;
 };
 
 // The tile in fp32 arithmetic, from the unscaled inputs and the weights put
 // back together: the path of inputs that are not finite.
-template <int MODE, int RT, int CT>
-__device__ __forceinline__ void conv_tile_f32(const SynthArgs& a, const void* wp, int nk, int ntap, int nkx, int b, const int (&qy)[RT],
-                              const int (&qx)[RT], int ct0, f4 (&acc)[RT][CT]) {
+template <int MODE, int RT, int CT, class QY, class QX>
+__device__ __forceinline__ void conv_tile_f32(const SynthArgs& a, const void* wp, int nk, int ntap, int nkx, int b, QY qy,
+                                              QX qx, int ct0, f4 (&acc)[RT][CT]) {
     const int lane = threadIdx.x & 63, kq = lane >> 4;
     const h8* w = static_cast<const h8*>(wp) + lane;
 #pragma unroll
@@ -314,7 +327,7 @@ __device__ __forceinline__ void conv_tile_f32(const SynthArgs& a, const void* wp
             for (int q = 0; q < 8; ++q) wf[q] = ldexpf((float)w0[q] + (float)w1[q], e);
 #pragma unroll
             for (int i = 0; i < RT; ++i) {
-                const int iy = qy[i] + dy, ix = qx[i] + dx;
+                const int iy = qy(i) + dy, ix = qx(i) + dx;
                 const bool ok = iy >= 0 && iy < a.Hi && ix >= 0 && ix < a.Wi && c < a.Ci;
                 const size_t q0 = (((size_t)b * a.Hi + iy) * a.Wi + ix) * a.Ci + c;
                 const f4 u = ld4<false>(a.in, q0, ok), v = ld4<false>(a.in, q0 + 4, ok);
@@ -329,23 +342,185 @@ __device__ __forceinline__ void conv_tile_f32(const SynthArgs& a, const void* wp
     }
 }
 
-template <class P, int MODE, int RT, int CT, int WC>
+// Inverse GDN of a workgroup that holds all channels of its pixels, x in acc
+// (lane: channels 4 (lane / 16) + q of each column tile, pixel lane % 16 of
+// each row tile): z = gamma x^2 + beta with the squares exchanged through LDS
+// as split operands, half of the row tiles at a time, then x sqrt(z) is
+// stored.  One pass over memory instead of three (the separate kernel wrote,
+// read and wrote the activations: third layer at 4K 2.45 + 1.31 ms, now 3.2).
+template <class P, int RT, int CT, class Store>
+__device__ __forceinline__ void gdn_epilogue(const SynthArgs& a, f4 (&acc)[RT][CT], int ct0, typename P::V* lds, unsigned* red,
+                                             unsigned* pmax, Store store) {
+    using V = typename P::V;
+    constexpr int NW = P::kNw, HR = RT / 2, HP = HR * kTile;   // row tiles and pixels of a half
+    const int lane = threadIdx.x & 63, kq = lane >> 4, nct = a.Cop / kTile, nch = (a.Co + 31) / 32;
+    int s = 0;
+    bool bad = false;
+    if constexpr (P::kScaled) {
+        unsigned pm[RT], m = 0;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            pm[i] = 0;
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) pm[i] = max(pm[i], abs_bits(acc[i][j][q] * acc[i][j][q]));
+            m = max(m, pm[i]);
+        }
+        m = block_max_bits(m, red);                      // (its barrier: the last patch has been read)
+        s = scale_exp(m);
+        bad = a.gforce || m >= kInfBits;
+        if (!bad && m > kSynthRange << 23 && m > __builtin_bit_cast(unsigned, a.covered)) {
+            // each pixel's largest square over all waves' channels
+            if (threadIdx.x < RT * kTile) pmax[threadIdx.x] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < RT; ++i) atomicMax(&pmax[i * kTile + (lane & 15)], pm[i]);
+            __syncthreads();
+            int low = 0;
+            if (threadIdx.x < RT * kTile) {
+                const unsigned v = pmax[threadIdx.x];
+                low = v != 0 && v < m - (kSynthRange << 23);
+            }
+            bad = __syncthreads_or(low);
+        }
+    } else {
+        __syncthreads();
+    }
+    const V* w = static_cast<const V*>(a.gwp) + lane;
+    size_t wo[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) wo[j] = (size_t)(ct0 + j < nct ? ct0 + j : 0) * nch * NW * 64;
+    auto load_w = [&](int c, V (&wv)[CT][NW]) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int n = 0; n < NW; ++n) wv[j][n] = w[wo[j] + (size_t)(c * NW + n) * 64];
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        V wv[CT][NW];
+        load_w(0, wv);
+        // operands [hi, lo][chunk][k-group][pixel] (bad: the squares in fp32, channels 0-3 and 4-7 of a group)
+#pragma unroll
+        for (int i = 0; i < HR; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                const f4 x = acc[h * HR + i][j], x2 = x * x;
+                const int n = (ct0 + j) * kTile + kq * 4;
+                if (n >= nch * 32) continue;             // (wave-uniform: a column tile past the last chunk)
+                const int at = (n >> 3) * HP + i * kTile + (lane & 15), lo = nch * 4 * HP;
+                if (bad) {
+                    *reinterpret_cast<f4*>(&lds[at + ((n & 4) ? lo : 0)]) = x2;
+                } else {
+                    typedef __attribute__((ext_vector_type(4))) unsigned short u4;
+                    u4 hi, lw;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if constexpr (P::kScaled) {
+                            const float v = ldexpf(x2[q], s);
+                            const _Float16 t = (_Float16)v;
+                            hi[q] = __builtin_bit_cast(unsigned short, t);
+                            lw[q] = __builtin_bit_cast(unsigned short, (_Float16)(v - (float)t));
+                        } else {
+                            hi[q] = bf16_bits(x2[q]);
+                            lw[q] = bf16_bits(x2[q] - bf16_value(hi[q]));
+                        }
+                    }
+                    *reinterpret_cast<u4*>(reinterpret_cast<unsigned short*>(&lds[at]) + (n & 4)) = hi;
+                    *reinterpret_cast<u4*>(reinterpret_cast<unsigned short*>(&lds[at + lo]) + (n & 4)) = lw;
+                }
+            }
+        __syncthreads();
+        f4 z[HR][CT];
+#pragma unroll
+        for (int i = 0; i < HR; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) z[i][j] = zero4();
+        const int lo = nch * 4 * HP;
+        if (P::kScaled && bad) {
+            if constexpr (P::kScaled)
+                for (int c = 0; c < nch; ++c)
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) {
+                        const V w0 = w[wo[j] + (size_t)(c * NW) * 64], w1 = w[wo[j] + (size_t)(c * NW + 1) * 64];
+                        const int e = ct0 + j < nct ? -a.gce[(ct0 + j) * kTile + (lane & 15)] : 0;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            const float wf = ldexpf((float)w0[q] + (float)w1[q], e);
+#pragma unroll
+                            for (int i = 0; i < HR; ++i) {
+                                const f4 x2 = *reinterpret_cast<const f4*>(&lds[(c * 4 + kq) * HP + i * kTile + (lane & 15) + (q < 4 ? 0 : lo)]);
+                                z[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf, x2[q & 3], z[i][j], 0, 0, 0);
+                            }
+                        }
+                    }
+        } else {
+            for (int c = 0; c < nch; ++c) {
+                if (c) load_w(c, wv);
+#pragma unroll
+                for (int i = 0; i < HR; ++i) {
+                    const int at = (c * 4 + kq) * HP + i * kTile + (lane & 15);
+                    const V hi = lds[at], lw = lds[at + lo];
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) z[i][j] = mfma_k32(wv[j][0], hi, z[i][j]);
+                    if constexpr (NW == 2) {
+#pragma unroll
+                        for (int j = 0; j < CT; ++j) z[i][j] = mfma_k32(wv[j][1], hi, z[i][j]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) z[i][j] = mfma_k32(wv[j][0], lw, z[i][j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int n = (ct0 + j) * kTile + kq * 4;
+            if (ct0 + j >= nct) continue;
+            const f4 beta = *reinterpret_cast<const f4*>(a.beta + n);
+            int4 e{0, 0, 0, 0};
+            if (P::kScaled && !bad) e = *reinterpret_cast<const int4*>(a.gce + n);
+#pragma unroll
+            for (int i = 0; i < HR; ++i) {
+                const f4 x = acc[h * HR + i][j];
+                f4 v = z[i][j];
+                if constexpr (P::kScaled)
+                    if (!bad) v = f4{ldexpf(v.x, -s - e.x), ldexpf(v.y, -s - e.y), ldexpf(v.z, -s - e.z), ldexpf(v.w, -s - e.w)};
+                v = v + beta;
+                store(h * HR + i, n, f4{x.x * sqrtf(v.x), x.y * sqrtf(v.y), x.z * sqrtf(v.z), x.w * sqrtf(v.w)});
+            }
+        }
+        if (h == 0) __syncthreads();                     // the first half's operands have been read
+    }
+}
+
+template <class P, int MODE, int RT, int CT, int WC, bool FUSE>
 __global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
     using V = typename P::V;
     using S = SynthShape<MODE, RT, CT, WC>;
     constexpr int NW = P::kNw, NI = S::kItems, NP = S::kPatch, HALO = S::kHalo;
-    __shared__ V patch[2][4][NP];                        // [hi, lo][k-group][pixel]
-    __shared__ unsigned red[4];
+    static_assert(!FUSE || (MODE == XM_DECONV && WC == 4), "a wave needs all pixels of the workgroup");
+    // the patch [hi, lo][k-group][pixel]; FUSE: also the squares of half of the pixels, all channels
+    constexpr int kGdn = FUSE ? 2 * (S::kCols / 8) * (S::kPx / 2) : 0;
+    __shared__ V patch[8 * NP > kGdn ? 8 * NP : kGdn];
+    __shared__ unsigned red[4], pmax[FUSE && P::kScaled ? S::kPx : 1];
 
-    // consecutive work on one XCD: the classes and column blocks of a tile,
-    // and neighbouring tiles, share patches in its L2
-    const int per = gridDim.x / kXcds;
-    int id = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-    if (id >= a.B * a.nty * a.ntx * a.ncls * a.ncb) return;
-    const int cb = id % a.ncb;
-    id /= a.ncb;
-    const int cls = id % a.ncls, py = cls >> 1, px = cls & 1;
-    id /= a.ncls;
+    // An XCD takes a run of neighbouring tiles, kSynthGroup of them at a time:
+    // their patches then stay in its L2 for all classes and column blocks.
+    // Within a group the class is the slowest index, the nine-tap class first:
+    // workgroups go to an XCD's four shader engines in turn, so with the class
+    // fastest one engine would get all of the nine-tap ones (measured: 2.90 ms
+    // for the third layer of a 4K image), and the last workgroups of a launch
+    // are then the short ones.
+    const int ntiles = a.B * a.nty * a.ntx, per = (ntiles + kXcds - 1) / kXcds;
+    int l = blockIdx.x / kXcds;
+    const int g0 = l / (kSynthGroup * a.ncls * a.ncb) * kSynthGroup, gn = min(kSynthGroup, per - g0);
+    l -= g0 * a.ncls * a.ncb;
+    const int cls = l / (gn * a.ncb), py = cls >> 1, px = cls & 1;
+    l -= cls * gn * a.ncb;
+    const int cb = l % a.ncb;
+    int id = (blockIdx.x % kXcds) * per + g0 + l / a.ncb;
+    if (id >= ntiles) return;
     const int tx = id % a.ntx;
     id /= a.ntx;
     const int ty = id % a.nty, b = id / a.nty;
@@ -400,7 +575,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
     const int r0 = wr * RT * kTile + (lane & 15);
     const int at0 = kq * NP + (r0 >> a.twl) * PW + (r0 & (TW - 1));
     const int step = MODE == XM_GDN ? kTile : (kTile >> a.twl) * PW;
-    const V* lds = &patch[0][0][0];
 
     f4 acc[RT][CT];
 #pragma unroll
@@ -457,23 +631,25 @@ __global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
                     hi = p.hi;
                     lo = p.lo;
                 }
-                patch[0][e & 3][e >> 2] = hi;
-                patch[1][e & 3][e >> 2] = lo;
+                patch[(e & 3) * NP + (e >> 2)] = hi;
+                patch[(4 + (e & 3)) * NP + (e >> 2)] = lo;
             }
         }
         __syncthreads();
-        if (ch + 1 < a.nch) load_chunk(ch + 1);
         int tap = 0;
         for (int t0 = 0; t0 < nky; ++t0)
             for (int t1 = 0; t1 < nkx; ++t1, ++tap) {
                 const int k = ch * ntap + tap;
+                // (pinned: the compiler would sink these loads to just before their use)
                 load_w(min(k + 1, nk - 1), wn);
+                if (tap == 0 && ch + 1 < a.nch) load_chunk(ch + 1);
+                __builtin_amdgcn_sched_barrier(0);
                 // patch row and column of this tap's pixel: dy + 1 and dx + 1
                 const int oy = MODE == XM_DECONV ? 2 - t0 : t0, ox = MODE == XM_DECONV ? 2 - t1 : t1;
                 const int at = at0 + (MODE == XM_GDN ? 0 : oy * PW + ox);
 #pragma unroll
                 for (int i = 0; i < RT; ++i) {
-                    const V hi = lds[at + i * step], lo = lds[4 * NP + at + i * step];
+                    const V hi = patch[at + i * step], lo = patch[4 * NP + at + i * step];
 #pragma unroll
                     for (int j = 0; j < CT; ++j) acc[i][j] = mfma_k32(wv[j][0], hi, acc[i][j]);
                     if constexpr (NW == 2) {
@@ -490,13 +666,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
             }
     }
 
-    int qy[RT], qx[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        const int r = r0 + i * kTile;
-        qy[i] = y0 + (r >> a.twl);
-        qx[i] = x0 + (r & (TW - 1));
-    }
+    auto qy = [&](int i) { return y0 + ((r0 + i * kTile) >> a.twl); };   // row tile i's pixel of this lane
+    auto qx = [&](int i) { return x0 + ((r0 + i * kTile) & (TW - 1)); };
     if constexpr (P::kScaled) {
         if (!bad && big > kSynthRange << 23 && (MODE != XM_GDN || big > __builtin_bit_cast(unsigned, a.covered))) {
             int low = 0;
@@ -514,35 +685,55 @@ __global__ __launch_bounds__(kThreads, 2) void k_synth(SynthArgs a) {
         }
     }
     // a lane holds channels 4 (lane / 16) + q of each column tile, pixel lane % 16
+    auto inside = [&](int i) { return qy(i) < a.Hi && qx(i) < a.Wi; };
+    auto store = [&](int i, int n, f4 v) {
+        const int oy = MODE == XM_DECONV ? 2 * qy(i) + py : qy(i), ox = MODE == XM_DECONV ? 2 * qx(i) + px : qx(i);
+        if (inside(i)) *reinterpret_cast<f4*>(a.out + (((size_t)b * a.Ho + oy) * a.Wo + ox) * a.Co + n) = v;
+    };
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+        const bool cv = ct0 + j < nct;                   // (wave-uniform)
+        const int n = (cv ? ct0 + j : 0) * kTile + kq * 4;
+        const f4 add = *reinterpret_cast<const f4*>(a.bias + n);
+        if constexpr (P::kScaled) {
+            const int4 ce = *reinterpret_cast<const int4*>(a.ce + n);
+            const int4 e = bad ? int4{0, 0, 0, 0} : int4{-s - ce.x, -s - ce.y, -s - ce.z, -s - ce.w};
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                acc[i][j] = f4{ldexpf(acc[i][j].x, e.x), ldexpf(acc[i][j].y, e.y), ldexpf(acc[i][j].z, e.z), ldexpf(acc[i][j].w, e.w)};
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            acc[i][j] = acc[i][j] + add;
+            // inverse GDN of the workgroup: zeros off the grid and past the last channel
+            if (FUSE) acc[i][j] = cv && inside(i) ? acc[i][j] : zero4();
+        }
+    }
+    if constexpr (FUSE) {
+        gdn_epilogue<P, RT, CT>(a, acc, ct0, patch, red, pmax, store);
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
         const int n = (ct0 + j) * kTile + kq * 4;
         if (ct0 + j >= nct) continue;
-        const f4 add = *reinterpret_cast<const f4*>(a.bias + n);
-        int4 e{0, 0, 0, 0};
-        if (P::kScaled && !bad) e = *reinterpret_cast<const int4*>(a.ce + n);
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-            if (qy[i] >= a.Hi || qx[i] >= a.Wi) continue;
             f4 v = acc[i][j];
-            if constexpr (P::kScaled)
-                if (!bad) v = f4{ldexpf(v.x, -s - e.x), ldexpf(v.y, -s - e.y), ldexpf(v.z, -s - e.z), ldexpf(v.w, -s - e.w)};
-            v = v + add;
             if (MODE == XM_DECONV4) {                    // columns (class, channel)
+                if (!inside(i)) continue;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int c4 = (n + q) / a.Co, c = n + q - c4 * a.Co;
                     if (c4 < 4)
-                        a.out[(((size_t)b * a.Ho + 2 * qy[i] + (c4 >> 1)) * a.Wo + 2 * qx[i] + (c4 & 1)) * a.Co + c] = v[q];
+                        a.out[(((size_t)b * a.Ho + 2 * qy(i) + (c4 >> 1)) * a.Wo + 2 * qx(i) + (c4 & 1)) * a.Co + c] = v[q];
                 }
             } else {
-                const int oy = MODE == XM_DECONV ? 2 * qy[i] + py : qy[i], ox = MODE == XM_DECONV ? 2 * qx[i] + px : qx[i];
-                const size_t o = (((size_t)b * a.Ho + oy) * a.Wo + ox) * a.Co + n;
-                if (MODE == XM_GDN) {
-                    const f4 x = *reinterpret_cast<const f4*>(a.in + o);
+                if (MODE == XM_GDN && inside(i)) {
+                    const f4 x = *reinterpret_cast<const f4*>(a.in + (size_t)qx(i) * a.Co + n);
                     v = f4{x.x * sqrtf(v.x), x.y * sqrtf(v.y), x.z * sqrtf(v.z), x.w * sqrtf(v.w)};
                 }
-                *reinterpret_cast<f4*>(a.out + o) = v;
+                store(i, n, v);
             }
         }
     }
@@ -764,47 +955,53 @@ static int synth_tiles(SynthArgs& a, int twl) {
     return a.ntx * a.nty;
 }
 
-template <class P, int MODE, int RT, int CT, int WC>
+template <class P, int MODE, int RT, int CT, int WC, bool FUSE = false>
 static void launch_synth(SynthArgs a, hipStream_t st) {
     using S = SynthShape<MODE, RT, CT, WC>;
     if (!S::kHalo) synth_tiles<S>(a, S::kPx == 128 ? 7 : 6);
     else if (synth_tiles<S>(a, 3) >= synth_tiles<S>(a, 4)) synth_tiles<S>(a, 4);   // the shape that pads less
     else synth_tiles<S>(a, 3);
     a.ncb = ceil_div(a.Cop, S::kCols);
-    const int n = a.B * a.nty * a.ntx * a.ncls * a.ncb;
-    hipLaunchKernelGGL((k_synth<P, MODE, RT, CT, WC>), dim3(ceil_div(n, kXcds) * kXcds), dim3(kThreads), 0, st, a);
+    const int per = ceil_div(a.B * a.nty * a.ntx, kXcds);
+    hipLaunchKernelGGL((k_synth<P, MODE, RT, CT, WC, FUSE>), dim3(kXcds * per * a.ncls * a.ncb), dim3(kThreads), 0, st, a);
 }
 
-template <class P, int MODE>
-static void run_synth_mode(const SynthArgs& a, hipStream_t st) {
-    const long long px = (long long)a.B * a.Hi * a.Wi * a.ncls;
-    // 128 pixels x 192 or 128 channels, whichever pads fewer columns, unless
-    // that leaves compute units without a workgroup: then 64 x 64.
-    const int n3 = ceil_div(a.Cop, 192), n2 = ceil_div(a.Cop, 128);
-    const bool wide = n3 * 192 <= n2 * 128;
-    if (px / 128 * (wide ? n3 : n2) < kSynthMinBlocks) launch_synth<P, MODE, 4, 1, 4>(a, st);
-    else if (wide) launch_synth<P, MODE, 8, 3, 4>(a, st);
-    else launch_synth<P, MODE, 8, 2, 4>(a, st);
-}
-
-// One layer of g_s: [B][h][w][Ci] -> [B][2h][2w][Co] (GDN: the same grid).
-template <class P>
-static void run_synth(const Layer& L, const float* in, float* out, int B, int h, int w, hipStream_t st) {
+static SynthArgs synth_args(const Layer& L, const float* in, float* out, int B, int h, int w) {
     SynthArgs a{};
     a.in = in; a.out = out; a.bias = L.bias; a.ce = L.ce; a.force_f32 = L.force_f32; a.covered = L.covered;
     for (int c = 0; c < 4; ++c) a.wp[c] = L.wp[c];
     a.Ci = L.Ci; a.Co = L.Co; a.Cop = L.Cop; a.nch = ceil_div(L.Ci, 32);
-    a.B = B; a.Hi = h; a.Wi = w; a.Ho = 2 * h; a.Wo = 2 * w; a.ncls = 1;
-    if (L.mode == XM_DECONV) {
-        a.ncls = 4;
-        run_synth_mode<P, XM_DECONV>(a, st);
-    } else if (L.mode == XM_GDN) {
-        a.B = a.Hi = a.Ho = 1;
-        a.Wi = a.Wo = B * h * w;
-        run_synth_mode<P, XM_GDN>(a, st);
-    } else {
-        launch_synth<P, XM_DECONV4, 2, 1, 1>(a, st);
+    a.B = B; a.Hi = h; a.Wi = w; a.Ho = 2 * h; a.Wo = 2 * w; a.ncls = L.mode == XM_DECONV ? 4 : 1;
+    return a;
+}
+
+// A transposed conv and its inverse GDN, [B][h][w][Ci] -> [B][2h][2w][Co]:
+// in one kernel into `other` where a workgroup of 128 pixels holds every
+// channel (up to 192) and the grid gives every compute unit a workgroup.
+// Otherwise the conv writes `other` and the GDN `own`, the buffer that may hold
+// the conv's input.  Returns the output.
+template <class P>
+static float* run_synth(const Layer& L, const Layer& G, const float* in, float* own, float* other, int B, int h, int w,
+                        hipStream_t st) {
+    SynthArgs a = synth_args(L, in, other, B, h, w);
+    const long long nb = 4LL * B * h * w / 128;
+    if (nb >= kSynthMinBlocks && L.Cop <= 192) {
+        a.gwp = G.wp[0]; a.gce = G.ce; a.beta = G.bias; a.gforce = G.force_f32; a.covered = G.covered;
+        if (L.Cop <= 128) launch_synth<P, XM_DECONV, 8, 2, 4, true>(a, st);
+        else launch_synth<P, XM_DECONV, 8, 3, 4, true>(a, st);
+        return other;
     }
+    SynthArgs g = synth_args(G, other, own, 1, 1, B * 4 * h * w);
+    g.Ho = 1;
+    g.Wo = g.Wi;
+    if (nb * ceil_div(L.Cop, 192) >= kSynthMinBlocks) {
+        launch_synth<P, XM_DECONV, 8, 3, 4>(a, st);
+        launch_synth<P, XM_GDN, 8, 3, 4>(g, st);
+    } else {
+        launch_synth<P, XM_DECONV, 4, 1, 4>(a, st);
+        launch_synth<P, XM_GDN, 4, 1, 4>(g, st);
+    }
+    return own;
 }
 
 template <class P>
@@ -819,14 +1016,15 @@ template <class P>
 static void synth(const Xform& x, const float* y, float* img, hipStream_t st) {
     int h = x.H, w = x.W;
     const float* in = y;
+    float *own = x.g_b, *other = x.g_a;
     for (int k = 0; k < 3; ++k) {
-        run_synth<P>(x.gs[k], in, x.g_a, x.B, h, w, st);
+        float* out = run_synth<P>(x.gs[k], x.gdn[k], in, own, other, x.B, h, w, st);
+        if (out == other) std::swap(own, other);
+        in = out;
         h *= 2;
         w *= 2;
-        run_synth<P>(x.gdn[k], x.g_a, x.g_b, x.B, h, w, st);
-        in = x.g_b;
     }
-    run_synth<P>(x.gs[3], in, img, x.B, h, w, st);
+    launch_synth<P, XM_DECONV4, 2, 1, 1>(synth_args(x.gs[3], in, img, x.B, h, w), st);
 }
 
 static void free_xform(Xform* x) {

@@ -110,10 +110,12 @@ def test_transforms_4k_full_size(precision):
 # 32 pixels, channel counts of one and several column blocks with and without
 # padding (48: 3 tiles of 16; 80; 144; 192 and 208 around a 192-channel block)
 # and M off the 32-channel chunk, on grids small enough for the 64-pixel tiles
-# and wide enough for the 128-pixel ones.  The bar is the one above.
+# and wide enough for the 128-pixel ones, with the inverse GDN in the conv
+# kernel (256 workgroups of 128 pixels in a layer, at most 192 channels) and
+# apart.  The bar is the one above.
 @pytest.mark.parametrize("precision,N,M,B,H,W", [
     ("fp32", 16, 32, 1, 1, 17), ("fp32", 48, 96, 2, 7, 9), ("fp32", 80, 32, 1, 17, 15), ("fp32", 144, 32, 1, 33, 31),
-    ("fp32", 208, 32, 1, 9, 40), ("fp32", 192, 64, 3, 31, 33), ("bf16", 32, 64, 1, 15, 17), ("bf16", 192, 64, 1, 31, 33),
+    ("fp32", 80, 32, 1, 33, 31), ("fp32", 208, 32, 1, 9, 40), ("fp32", 192, 64, 3, 31, 33), ("bf16", 32, 64, 1, 15, 17), ("bf16", 192, 64, 1, 31, 33),
     ("bf16", 96, 64, 2, 8, 16),
 ])
 def test_synthesis_tile_edges(precision, N, M, B, H, W):
@@ -126,12 +128,13 @@ def test_synthesis_tile_edges(precision, N, M, B, H, W):
     check(got, T.synthesis(y, w), precision, "image")
 
 
+@pytest.mark.parametrize("H,W", [(9, 11), (27, 33)])   # inverse GDN apart; in the third layer's conv kernel
 @pytest.mark.parametrize("scale", [1e-12, 1e-3, 300.0])   # (inverse GDN squares three times: more overflows fp32)
-def test_synthesis_scales(scale):
+def test_synthesis_scales(scale, H, W):
     """Inputs of any magnitude: the products run on f16 pairs scaled by the
     patch's largest value, which grows from chunk to chunk here (32 channels
     each), so accumulators are rescaled.  The bar is the one above."""
-    N, M, H, W = 48, 160, 9, 11
+    N, M = 48, 160
     w = inputs.make_transform_weights(N, M)
     y = np.random.default_rng(10).normal(size=(1, H, W, M)) * np.repeat(4.0 ** np.arange(-2, 3), 32) * scale
     y = y.astype(np.float32)
@@ -141,27 +144,29 @@ def test_synthesis_scales(scale):
     check(got, T.synthesis(y, w), "fp32", f"image of latents scaled by {scale}")
 
 
-@pytest.mark.parametrize("where", ["latent", "weight"])
+@pytest.mark.parametrize("H,W", [(12, 20), (24, 40)])   # inverse GDN apart; in the third layer's conv kernel
+@pytest.mark.parametrize("where", ["latent", "weight", "gamma"])
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38, 1e9])
-def test_synthesis_not_finite(value, where):
+def test_synthesis_not_finite(value, where, H, W):
     """An infinity, a NaN or a value whose square overflows reaches the same
     outputs as in the oracle (in 64 bits: 3e38 and 1e9 have to be lost where
     fp32 overflows), and no output beyond its receptive field: the pixels
     beside an outlier keep their precision."""
-    N, M, H, W = 32, 32, 12, 20
+    N, M = 32, 32
     w = inputs.make_transform_weights(N, M)
     y = np.random.default_rng(11).normal(scale=2.0, size=(1, H, W, M)).astype(np.float32)
     if where == "latent":
         y[0, 4, 6, 5] = value
     else:
-        w["gs1_w"] = w["gs1_w"].copy()
-        w["gs1_w"][3, 2, 0, 0] = value
+        name, at = {"weight": ("gs1_w", (3, 2, 0, 0)), "gamma": ("gdn3_gamma", (4, 7))}[where]
+        w[name] = w[name].copy()
+        w[name][at] = abs(value)
     x = wf.Xform(w, N, M, 1, H, W, "fp32")
     got = x.synthesis(torch.from_numpy(y).cuda()).cpu().numpy()
     x.close()
     ref = T.synthesis(y, w)
     lost = ~np.isfinite(ref) | (np.abs(ref) > 1e37)
-    assert lost.any()
+    assert lost.any() or where == "gamma"
     assert not np.isfinite(got[lost]).any() or (np.abs(got[lost][np.isfinite(got[lost])]) > 1e30).all()
     if where == "latent":
         away = np.ones_like(lost)
