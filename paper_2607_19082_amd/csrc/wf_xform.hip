@@ -34,150 +34,228 @@ namespace wf {
 
 enum { XM_DECONV = 0, XM_CONV3 = 1, XM_GDN = 2, XM_DECONV4 = 3 };
 
+// ---- the hyper-decoder's layers ------------------------------------------------
+//
+// psi feeds the entropy parameters, and an encoder and a decoder have to agree
+// on every bit of them, so these layers keep fp32 MFMA and one accumulation
+// order per output, whatever the tile: the taps in raster order, each tap's
+// input channels ascending.  Bound by the matrix cores (248 GFLOP at 4K,
+// 157 TFLOP/s) on large grids, by the length of that chain on small ones.
+//
+// A workgroup owns 16 RT WR pixels of one class and 16 CT WC channels.  Each
+// step is one tap's chunk of 32 input channels: its pixels are staged in LDS
+// in operand order ([operand][k-group][pixel], 16 bytes each), double-buffered
+// with one barrier a step, the loads two steps ahead of their use; weights
+// come from L2 in operand order, also two steps ahead.  The four MFMAs of an
+// fp32 k-block go round the wave's tiles, so that consecutive ones do not
+// depend on each other.  Weights are the first operand: a lane holds four
+// consecutive channels of one pixel and stores 16 bytes.  4K (N = 192,
+// M = 320): 3.03 ms before (operands loaded per wave, 128 x 64 tiles, one
+// k-block's MFMAs in a chain), 2.04 now (122 TFLOP/s); a 32x48 latent
+// (N = 128, M = 192) 291 -> 100 us.
 struct ConvArgs {
     const float* in;
     float* out;
     const void* wp[4];        // packed panel per output class
-    const float* bias;        // [Co] (deconv, conv)
-    const float* beta;        // [Co] (GDN)
+    const float* bias;        // [Co]
     int B, Hi, Wi, Ci;        // input [B][Hi][Wi][Ci]
     int Hq, Wq;               // output pixels of one class per image (rows = B Hq Wq)
     int Co, Cop;              // output channels, and padded to whole column tiles
     int Ho, Wo;               // output array [B][Ho][Wo][Co]; pixels outside are not stored
     int relu;
+    int nrb, ncb;             // row and column blocks
 };
 
-// Rows: RTW row tiles per wave, 4 / WCOL waves along the rows; columns: CTW
-// column tiles per wave, WCOL waves along the columns.
-template <int RTW, int CTW, int WCOL>
+template <int RT, int CT, int WC>
 struct ConvShape {
-    static constexpr int kRowTiles = RTW * (4 / WCOL), kColTiles = CTW * WCOL;
+    static constexpr int kWr = 4 / WC;                         // waves along the pixels
+    static constexpr int kPx = 16 * RT * kWr, kCols = 16 * CT * WC;
+    static constexpr int kItems = (kPx * 4 + kThreads - 1) / kThreads;   // 8-channel pieces a thread stages
 };
 
-template <class P, int MODE, int RTW, int CTW, int WCOL>
-__global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
-    using A = typename P::A;
+template <class P, int MODE, int RT, int CT, int WC>
+__global__ __launch_bounds__(kThreads, 2) void k_conv(ConvArgs a) {
     using Bw = typename P::B;
-    using S = ConvShape<RTW, CTW, WCOL>;
-    constexpr int KB = RTW == 4 || P::kBf16 ? 6 : 8;   // k-blocks in flight per wave
-    const int cls = blockIdx.z, py = cls >> 1, px = cls & 1;
-    const int nky = MODE == XM_DECONV ? (py ? 2 : 3) : (MODE == XM_GDN ? 1 : 3);
-    const int nkx = MODE == XM_DECONV ? (px ? 2 : 3) : (MODE == XM_GDN ? 1 : 3);
-    const int cbn = a.Ci / P::kK;                        // k-blocks per tap
-    const int nkb = nky * nkx * cbn;
+    using S = ConvShape<RT, CT, WC>;
+    constexpr int NI = S::kItems, PX = S::kPx, NB = 32 / P::kK;   // weight k-blocks of a chunk
+    constexpr bool DEEP = RT * CT * NB < 16;                      // weights two steps ahead (else one: registers)
+    __shared__ f4 tile[2][8][PX];      // fp32: [k-block][k-group]; bf16: [hi, lo][k-group]
+    // neighbouring rows on one XCD, the column blocks of a row block together
+    const int per = (a.nrb + kXcds - 1) / kXcds, l = blockIdx.x / kXcds;
+    const int rb = (blockIdx.x % kXcds) * per + l / a.ncb, cb = l % a.ncb;
+    if (rb >= a.nrb) return;
+    const int cls = blockIdx.y, py = cls >> 1, px = cls & 1;
+    const int nky = MODE == XM_DECONV && py ? 2 : 3, nkx = MODE == XM_DECONV && px ? 2 : 3;
+    const int nch = (a.Ci + 31) / 32, ns = nky * nkx * nch;       // steps
+    const int cbn = a.Ci / P::kK, nkb = nky * nkx * cbn;          // weight k-blocks of a tap, of all
     const int nrows = a.B * a.Hq * a.Wq, nct = a.Cop / kTile;
-    const int ncb = (nct + S::kColTiles - 1) / S::kColTiles;
-    const int cb = blockIdx.x % ncb, rb = blockIdx.x / ncb;
     const int wave = wave_id(), lane = threadIdx.x & 63, kq = lane >> 4;
-    const int wr = wave / WCOL, wc = wave % WCOL;
-    const int rt0 = rb * S::kRowTiles + wr * RTW, ct0 = cb * S::kColTiles + wc * CTW;
-    if (rt0 * kTile >= nrows) return;                    // (whole wave past the rows; no barrier below)
+    const int wr = wave / WC, wc = wave % WC, ct0 = (cb * WC + wc) * CT;
 
-    int rb_[RTW], ry[RTW], rx[RTW];
-    bool rv[RTW];
+    // staged pieces of this thread: pixel e / 4, channels 8 (e % 4) .. + 8
+    int iy[NI], ix[NI], at[NI];
 #pragma unroll
-    for (int i = 0; i < RTW; ++i) {
-        const int r = (rt0 + i) * kTile + (lane & 15);
-        rv[i] = r < nrows;
-        const int rr = rv[i] ? r : 0;
-        rb_[i] = rr / (a.Hq * a.Wq);
-        const int rem = rr - rb_[i] * a.Hq * a.Wq;
-        ry[i] = rem / a.Wq;
-        rx[i] = rem - ry[i] * a.Wq;
+    for (int n = 0; n < NI; ++n) {
+        const int e = threadIdx.x + n * kThreads, r = rb * PX + (e >> 2);
+        const bool ok = e < PX * 4 && r < nrows;
+        const int rr = ok ? r : 0, b = rr / (a.Hq * a.Wq), rem = rr - b * a.Hq * a.Wq;
+        iy[n] = ok ? rem / a.Wq : -4;                             // (-4: no tap of it lies on the grid)
+        ix[n] = rem - rem / a.Wq * a.Wq;
+        at[n] = ((b * a.Hi + rem / a.Wq) * a.Wi + ix[n]) * a.Ci + (e & 3) * 8;
     }
-    const Bw* w[CTW];
-    bool cv[CTW];
+    struct Stage {
+        f4 u[NI], v[NI];
+    };
+    // step s: tap (ty, tx), chunk ch
+    auto load_in = [&](int ty, int tx, int ch, Stage& st) {
+        const int dy = MODE == XM_DECONV ? 1 - ty : ty - 1, dx = MODE == XM_DECONV ? 1 - tx : tx - 1;
+        const int off = (dy * a.Wi + dx) * a.Ci + ch * 32;
 #pragma unroll
-    for (int j = 0; j < CTW; ++j) {
-        cv[j] = ct0 + j < nct;                           // wave-uniform
-        w[j] = static_cast<const Bw*>(a.wp[cls]) + (size_t)(cv[j] ? ct0 + j : 0) * nkb * 64 + lane;
-    }
-    auto la = [&](int i, int kb) -> A {
-        const int t = kb / cbn;
-        const int c0 = (kb - t * cbn) * P::kK + kq * (P::kK / 4);
-        int dy = 0, dx = 0;
-        if (MODE == XM_DECONV) {
-            const int ty = t / nkx;
-            dy = 1 - ty;
-            dx = 1 - (t - ty * nkx);
-        } else if (MODE == XM_CONV3 || MODE == XM_DECONV4) {
-            const int ty = t / 3;
-            dy = ty - 1;
-            dx = t - ty * 3 - 1;
-        }
-        const int iy = ry[i] + dy, ix = rx[i] + dx;
-        const bool ok = rv[i] && iy >= 0 && iy < a.Hi && ix >= 0 && ix < a.Wi;
-        const size_t q = (((size_t)rb_[i] * a.Hi + iy) * a.Wi + ix) * a.Ci + c0;
-        if constexpr (P::kBf16) {
-            f4 u = ld4<false>(a.in, q, ok), v = ld4<false>(a.in, q + 4, ok);
-            if (MODE == XM_GDN) {
-                u = u * u;
-                v = v * v;
-            }
-            return split8(u, v);
-        } else {
-            f4 u = ld4<false>(a.in, q, ok);
-            if (MODE == XM_GDN) u = u * u;
-            return u;
+        for (int n = 0; n < NI; ++n) {
+            const int y = iy[n] + dy, x = ix[n] + dx;
+            const bool ok = y >= 0 && y < a.Hi && x >= 0 && x < a.Wi && ch * 32 + (threadIdx.x & 3) * 8 < a.Ci;
+            st.u[n] = ld4<false>(a.in, (size_t)(at[n] + off), ok);
+            st.v[n] = ld4<false>(a.in, (size_t)(at[n] + off + 4), ok);
         }
     };
-    f4 acc[RTW][CTW];
+    auto stage = [&](const Stage& st, f4 (*t)[PX]) {
 #pragma unroll
-    for (int i = 0; i < RTW; ++i)
-#pragma unroll
-        for (int j = 0; j < CTW; ++j) acc[i][j] = zero4();
-    for (int kc = 0; kc < nkb; kc += KB) {
-        A av[KB][RTW];
-        Bw bv[KB][CTW];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            const int k = min(kc + u, nkb - 1);
-#pragma unroll
-            for (int i = 0; i < RTW; ++i) av[u][i] = la(i, k);
-#pragma unroll
-            for (int j = 0; j < CTW; ++j) bv[u][j] = w[j][(size_t)k * 64];
-        }
-#pragma unroll
-        for (int u = 0; u < KB; ++u)
-            if (kc + u < nkb)
-#pragma unroll
-                for (int i = 0; i < RTW; ++i)
-#pragma unroll
-                    for (int j = 0; j < CTW; ++j) acc[i][j] = P::mma(av[u][i], bv[u][j], acc[i][j]);
-    }
-    // lane holds rows 4*(lane/16) + q of each row tile, column lane%16
-#pragma unroll
-    for (int j = 0; j < CTW; ++j) {
-        const int cc = (ct0 + j) * kTile + (lane & 15);   // column: channel, or (class, channel)
-        const int ccls = MODE == XM_DECONV4 ? cc / a.Co : 0;
-        const int c = MODE == XM_DECONV4 ? cc - ccls * a.Co : cc;
-        if (!cv[j] || c >= a.Co || ccls >= 4) continue;
-        const float add = MODE == XM_GDN ? a.beta[c] : a.bias[c];
-#pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int ro = (rt0 + i) * kTile + kq * 4 + q;
-                if (ro >= nrows) continue;
-                const int b = ro / (a.Hq * a.Wq), rem = ro - b * a.Hq * a.Wq;
-                const int qy = rem / a.Wq, qx = rem - qy * a.Wq;
-                int oy = qy, ox = qx;
-                if (MODE == XM_DECONV) {
-                    oy = 2 * qy + py;
-                    ox = 2 * qx + px;
-                } else if (MODE == XM_DECONV4) {
-                    oy = 2 * qy + (ccls >> 1);
-                    ox = 2 * qx + (ccls & 1);
-                }
-                if (oy >= a.Ho || ox >= a.Wo) continue;
-                float v = acc[i][j][q] + add;
-                if (MODE == XM_GDN) {
-                    v = a.in[(((size_t)b * a.Hi + qy) * a.Wi + qx) * a.Ci + c] * sqrtf(v);
-                } else if (a.relu) {
-                    v = fmaxf(v, 0.0f);
-                }
-                a.out[(((size_t)b * a.Ho + oy) * a.Wo + ox) * a.Co + c] = v;
+        for (int n = 0; n < NI; ++n) {
+            const int e = threadIdx.x + n * kThreads, p = e >> 2, g = e & 3;
+            if (PX * 4 % kThreads && e >= PX * 4) continue;
+            if constexpr (P::kBf16) {
+                const b8x2 h = split8(st.u[n], st.v[n]);
+                t[g][p] = __builtin_bit_cast(f4, h.hi);
+                t[4 + g][p] = __builtin_bit_cast(f4, h.lo);
+            } else {
+                t[g * 2][p] = st.u[n];                            // (channels 8 g .. : k-block g / 2)
+                t[g * 2 + 1][p] = st.v[n];
             }
+        }
+    };
+    const Bw* w = static_cast<const Bw*>(a.wp[cls]) + lane;
+    size_t wo[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) wo[j] = (size_t)(ct0 + j < nct ? ct0 + j : 0) * nkb * 64;
+    struct Weights {
+        Bw w[CT][NB];
+    };
+    auto load_w = [&](int tap, int ch, Weights& wv) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const int k = min(tap * cbn + ch * NB + n, nkb - 1);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) wv.w[j][n] = w[wo[j] + (size_t)k * 64];
+        }
+    };
+    f4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = zero4();
+    const int r0 = wr * RT * kTile + (lane & 15);
+    auto products = [&](int ch, const Weights& wv, const f4 (*t)[PX]) {
+        if constexpr (P::kBf16) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const b8 hi = __builtin_bit_cast(b8, t[kq][r0 + i * kTile]);
+                const b8 lo = __builtin_bit_cast(b8, t[4 + kq][r0 + i * kTile]);
+#pragma unroll
+                for (int j = 0; j < CT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.w[j][0], hi, acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < CT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.w[j][0], lo, acc[i][j], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                if (n && ch * 32 + 16 >= a.Ci) break;             // (Ci = 16 mod 32: the last chunk is half)
+                f4 x[RT];
+#pragma unroll
+                for (int i = 0; i < RT; ++i) x[i] = t[n * 4 + kq][r0 + i * kTile];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+#pragma unroll
+                        for (int j = 0; j < CT; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w[j][n][q], x[i][q], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+
+    // Steps in order of (tap, chunk); `q*` is the step being loaded, two ahead
+    // of the products (past the end: the last one again, not used).
+    int ch = 0, qt = 0, qty = 0, qtx = 0, qch = 0, pt = 0, pch = 0;   // (p*: the step before q*)
+    auto advance = [&] {
+        pt = qt;
+        pch = qch;
+        if (++qch < nch) return;
+        if (qt + 1 == nky * nkx) {
+            qch = nch - 1;
+            return;
+        }
+        qch = 0;
+        ++qt;
+        if (++qtx == nkx) {
+            qtx = 0;
+            ++qty;
+        }
+    };
+    Stage s0, s1;
+    Weights w0, w1, w2;
+    load_in(0, 0, 0, s0);
+    load_w(0, 0, w0);
+    advance();
+    load_in(qty, qtx, qch, s1);
+    if (DEEP) load_w(qt, qch, w1);
+    advance();
+    stage(s0, tile[0]);
+    __syncthreads();
+    // one step: load step s + 2 into sl and step s + 2 (or s + 1) into wl,
+    // products of step s, stage step s + 1
+    auto step = [&](int s, Stage& sl, const Stage& sn, Weights& wl, const Weights& wu) {
+        load_w(DEEP ? qt : pt, DEEP ? qch : pch, wl);
+        load_in(qty, qtx, qch, sl);
+        advance();
+        __builtin_amdgcn_sched_barrier(0);
+        products(ch, wu, tile[s & 1]);
+        if (++ch == nch) ch = 0;
+        stage(sn, tile[(s & 1) ^ 1]);
+        __syncthreads();
+    };
+    if constexpr (DEEP) {
+        for (int s = 0; s < ns; s += 6) {
+            step(s, s0, s1, w2, w0);
+            if (s + 1 < ns) step(s + 1, s1, s0, w0, w1);
+            if (s + 2 < ns) step(s + 2, s0, s1, w1, w2);
+            if (s + 3 < ns) step(s + 3, s1, s0, w2, w0);
+            if (s + 4 < ns) step(s + 4, s0, s1, w0, w1);
+            if (s + 5 < ns) step(s + 5, s1, s0, w1, w2);
+        }
+    } else {
+        for (int s = 0; s < ns; s += 2) {
+            step(s, s0, s1, w1, w0);
+            if (s + 1 < ns) step(s + 1, s1, s0, w0, w1);
+        }
+    }
+
+    // a lane holds channels 4 (lane / 16) + q of each column tile, pixel lane % 16
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int r = rb * PX + r0 + i * kTile;
+        if (r >= nrows) continue;
+        const int b = r / (a.Hq * a.Wq), rem = r - b * a.Hq * a.Wq, qy = rem / a.Wq, qx = rem - qy * a.Wq;
+        const int oy = MODE == XM_DECONV ? 2 * qy + py : qy, ox = MODE == XM_DECONV ? 2 * qx + px : qx;
+        if (oy >= a.Ho || ox >= a.Wo) continue;
+        float* o = a.out + (((size_t)b * a.Ho + oy) * a.Wo + ox) * a.Co + kq * 4;
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            if (ct0 + j >= nct) continue;
+            const int n = (ct0 + j) * kTile;
+            f4 v = acc[i][j] + *reinterpret_cast<const f4*>(a.bias + n + kq * 4);
+            if (a.relu) v = f4{fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f), fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f)};
+            *reinterpret_cast<f4*>(o + n) = v;
+        }
     }
 }
 
@@ -916,6 +994,19 @@ static int xf_synth_gdn(Xform* x, Layer& L, const float* beta, const float* gamm
                          [&](int n) { return beta[n]; });
 }
 
+constexpr long long kConvSmall = 1000000, kConvMidF32 = 2600000, kConvMidBf16 = 2000000, kConvWide = 8000000;
+
+static int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+template <class P, int MODE, int RT, int CT, int WC>
+static void launch_conv(ConvArgs a, hipStream_t st) {
+    using S = ConvShape<RT, CT, WC>;
+    a.nrb = ceil_div(a.B * a.Hq * a.Wq, S::kPx);
+    a.ncb = ceil_div(a.Cop, S::kCols);
+    const dim3 grid(kXcds * ceil_div(a.nrb, kXcds) * a.ncb, MODE == XM_DECONV ? 4 : 1);
+    hipLaunchKernelGGL((k_conv<P, MODE, RT, CT, WC>), grid, dim3(kThreads), 0, st, a);
+}
+
 template <class P, int MODE>
 static void launch_layer(const Layer& L, const float* in, float* out, int B, int Hi, int Wi, int Hq, int Wq, int Ho,
                          int Wo, hipStream_t st) {
@@ -924,16 +1015,20 @@ static void launch_layer(const Layer& L, const float* in, float* out, int B, int
     for (int c = 0; c < 4; ++c) a.wp[c] = L.wp[c];
     a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ci = L.Ci; a.Hq = Hq; a.Wq = Wq;
     a.Co = L.Co; a.Cop = L.Cop; a.Ho = Ho; a.Wo = Wo; a.relu = L.relu;
-    const int nrows = B * Hq * Wq, nct = L.Cop / kTile, ncls = MODE == XM_DECONV ? 4 : 1;
-    // Row tiles per wave: 4 with fp32 operands (each weight operand then feeds
-    // four MFMA chains, which halves the weight reads against 2); bf16 pairs
-    // already hold twice the registers per operand and keep 2 (measured:
-    // 4 was 5% slower there).
-    constexpr int RTW = P::kBf16 ? 2 : 4;
-    using S = ConvShape<RTW, 2, 2>;      // 2 RTW row tiles x 4 column tiles per workgroup
-    const int nb = ((nrows + S::kRowTiles * kTile - 1) / (S::kRowTiles * kTile)) *
-                   ((nct + S::kColTiles - 1) / S::kColTiles);
-    hipLaunchKernelGGL((k_conv<P, MODE, RTW, 2, 2>), dim3(nb, 1, ncls), dim3(kThreads), 0, st, a);
+    const long long rows = (long long)B * Hq * Wq * (MODE == XM_DECONV ? 4 : 1);
+    // Pixels x channels of a workgroup by the layer's outputs, so that small
+    // layers still spread over the chip (us per layer, 16 x 64 / 32 x 64 / the
+    // larger tile).  fp32: 0.59 M outputs 56 / 64 / 67, 1.9 M 107 / 91 / 106,
+    // 3.9 M 211 / 191 / 158; 4K's 20.7 M 2000 / 1700 / 1560 (before: 2170),
+    // 128 x 160 1580.  bf16: 0.98 M 62 / 63 / 68, 2.4 M 145 / 96 / 89; 20.7 M
+    // 1060 / 680 / 473, and 405 with 128 x 160 (before: 1373), which only pays
+    // where 160 divides the channels (12.4 M outputs in 384: 197, 64 x 96 167).
+    const long long outputs = rows * L.Cop;
+    if (outputs < kConvSmall) launch_conv<P, MODE, 1, 1, 4>(a, st);
+    else if (outputs < (P::kBf16 ? kConvMidBf16 : kConvMidF32)) launch_conv<P, MODE, 2, 1, 4>(a, st);
+    else if constexpr (!P::kBf16) launch_conv<P, MODE, 4, 1, 4>(a, st);
+    else if (outputs >= kConvWide && L.Cop % 160 == 0) launch_conv<P, MODE, 4, 5, 2>(a, st);
+    else launch_conv<P, MODE, 2, 3, 2>(a, st);
 }
 
 template <class P>
@@ -942,8 +1037,6 @@ static void run_layer(const Layer& L, const float* in, float* out, int B, int Hi
     if (L.mode == XM_DECONV) launch_layer<P, XM_DECONV>(L, in, out, B, Hi, Wi, Hi, Wi, Ho, Wo, st);
     else launch_layer<P, XM_CONV3>(L, in, out, B, Hi, Wi, Ho, Wo, Ho, Wo, st);
 }
-
-static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Tiles of a launch: along x and y, for a tile 2^twl wide.
 template <class S>

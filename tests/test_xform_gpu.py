@@ -128,6 +128,23 @@ def test_synthesis_tile_edges(precision, N, M, B, H, W):
     check(got, T.synthesis(y, w), precision, "image")
 
 
+# The hyper-decoder's tiles: 16, 32 and 64 pixels (bf16 also 128) by 64 channels
+# (bf16 64 x 96, 128 x 160), chosen by a layer's outputs (1.0, 2.6 and, bf16,
+# 2.0 and 8.0 million); N or 3M/2 off the 32-channel chunk, grids off the tiles.
+@pytest.mark.parametrize("precision,N,M,B,H,W", [
+    ("fp32", 16, 32, 1, 5, 5), ("fp32", 48, 96, 1, 37, 41), ("fp32", 16, 160, 1, 61, 53), ("fp32", 48, 224, 1, 101, 67),
+    ("bf16", 32, 64, 2, 9, 21), ("bf16", 32, 192, 1, 61, 59), ("bf16", 32, 192, 1, 97, 67), ("bf16", 64, 320, 1, 97, 131),
+])
+def test_hyper_tile_edges(precision, N, M, B, H, W):
+    log(f"hyper case N={N} M={M} B={B} H={H} W={W} precision={precision}")
+    w = inputs.make_transform_weights(N, M)
+    z = inputs.make_zhat(B, -(-H // 4), -(-W // 4), N)
+    x = wf.Xform(w, N, M, B, H, W, precision)
+    got = x.hyper_synthesis(torch.from_numpy(z).cuda()).cpu().numpy()
+    x.close()
+    check(got, T.hyper_synthesis(z, w)[:, :H, :W], precision, "psi")
+
+
 @pytest.mark.parametrize("H,W", [(9, 11), (27, 33)])   # inverse GDN apart; in the third layer's conv kernel
 @pytest.mark.parametrize("scale", [1e-12, 1e-3, 300.0])   # (inverse GDN squares three times: more overflows fp32)
 def test_synthesis_scales(scale, H, W):
