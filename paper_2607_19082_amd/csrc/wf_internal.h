@@ -93,6 +93,7 @@ constexpr int kResMaxParts = 12;    // k-parts of the old-tap context (the last 
 // fp32 / 9.19 bf16, 256 bytes apart 9.92 / 8.45, 512 or 1024 no better;
 // 32 bytes apart, or packed, 12.4-16.5 ms.
 constexpr int kResSlotWords = 64;
+constexpr unsigned kResFill = 0xFFFFFFFFu;   // fill pattern of the resident fp32 h1 and h2
 constexpr int kResRep = 2;          // replicas of every weight slice (they take alternate tasks)
 constexpr int kResKbaseLds = 4096;  // largest T + 1 of a resident plan (its step table sits in LDS)
 constexpr int kResMinHoist = 8;     // fewest spare workgroups that compute the hoisted layer-1 part in the launch
@@ -261,6 +262,9 @@ struct Plan {
     DfArgs df{};
     // resident driver
     ResArgs res{};
+    const void* wp_split = nullptr;      // fp32: W1[:, :2M] as f16 pairs (wf_split.h), its columns' scale
+    const int* ce_split = nullptr;       // exponents, and whether a weight is not finite
+    int force_split = 0;
     // graph driver
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -310,10 +314,15 @@ int dataflow_deps(Plan& p, std::vector<int32_t>& out);
 int enqueue_dataflow(Plan& p, hipStream_t stream);
 const void* dataflow_fn(const Plan& p);
 // Resident driver: roles and buffers of the plan, and one call.
-int build_resident(Plan& p);
+// (w1: the layer-1 weights, host)
+int build_resident(Plan& p, const float* w1);
 // Tasks and waits of a plan's geometry, flattened (host only; wf_plan_deps).
 int resident_deps(const Plan& p, std::vector<int32_t>& out);
-int enqueue_resident(Plan& p, hipStream_t stream);
+// Its weights for, and the launch of, what precedes k_resident (wf_prep.hip):
+// the call's pointers, counters and fills, fp32: the hoisted part.
+int build_resident_prep(Plan& p, const float* w1);
+int enqueue_resident_prep(Plan& p, const CallPtrs& c, hipStream_t stream);
+int enqueue_resident(Plan& p, const CallPtrs& c, hipStream_t stream);
 // Grid of a cooperative kernel: two workgroups per CU when they fit, else one.
 int coop_grid(Plan& p, const void* fn, int* grid);
 // Latency floor of one dependent step hop (see wf_measure_floor).

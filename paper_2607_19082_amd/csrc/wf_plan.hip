@@ -438,7 +438,7 @@ static int build_plan(const wf_desc* d, Plan* p, bool geometry_only = false) {
         p->df.ncrit = p->grid >= 2 * kXcds ? p->grid / 2 / kXcds * kXcds : p->grid;
         if (p->df.ncrit == p->grid) return fail(WF_E_UNSUPPORTED, "dataflow driver needs at least 16 workgroups");
     }
-    if (p->driver == WF_DRIVER_RESIDENT && (rc = build_resident(*p)) != WF_OK) return rc;
+    if (p->driver == WF_DRIVER_RESIDENT && (rc = build_resident(*p, d->w1)) != WF_OK) return rc;
     if (d->entropy_coder == WF_EC_RANS && (rc = build_ec(p, d->scale_table, d->L)) != WF_OK) return rc;
     WF_HIP(hipDeviceSynchronize());
 
@@ -576,6 +576,7 @@ static int check_out(const Plan* p, const wf_out* out) {
 }
 
 static int run_call(Plan* p, const CallPtrs& c, hipStream_t stream, bool ec = false) {
+    if (p->driver == WF_DRIVER_RESIDENT && !ec) return enqueue_resident(*p, c, stream);
     int rc = enqueue_set_call(*p, c, stream);
     if (rc != WF_OK) return rc;
     if (p->driver == WF_DRIVER_GRAPH) {
@@ -585,7 +586,6 @@ static int run_call(Plan* p, const CallPtrs& c, hipStream_t stream, bool ec = fa
     if (ec) return enqueue_steps(*p, stream, true);
     if (p->driver == WF_DRIVER_PERSISTENT) return enqueue_persistent(*p, stream);
     if (p->driver == WF_DRIVER_DATAFLOW) return enqueue_dataflow(*p, stream);
-    if (p->driver == WF_DRIVER_RESIDENT) return enqueue_resident(*p, stream);
     return enqueue_steps(*p, stream);
 }
 

@@ -337,9 +337,8 @@ struct WSlice {
     }
 };
 
-// Whether an fp32 activation operand holds the fill pattern of h1 / h2 (an
-// all-ones word).
-constexpr unsigned kResFill = 0xFFFFFFFFu;
+// Whether an fp32 activation operand holds the fill pattern of h1 / h2
+// (kResFill).
 template <class P>
 constexpr bool kResChecked = !P::kBf16;
 __device__ __forceinline__ bool holds_fill(const f4& v) {
@@ -1173,17 +1172,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-__global__ void k_res_fill(unsigned* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = kResFill;
-}
-
-// Zero the n counter slots (only their first words).
-__global__ void k_res_zero(unsigned* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i * kResSlotWords] = 0u;
-}
-
 static const void* resident_fn(const Plan& p) {
     if (p.precision == WF_BF16)
         return p.K == 1 ? (const void*)k_resident<PBF16, 1> : (const void*)k_resident<PBF16, 3>;
@@ -1283,7 +1271,7 @@ int resident_deps(const Plan& p, std::vector<int32_t>& out) {
     return WF_OK;
 }
 
-int build_resident(Plan& p) {
+int build_resident(Plan& p, const float* w1) {
     const StepArgs& a = p.args;
     ResArgs& r = p.res;
     const bool bf = p.precision == WF_BF16;
@@ -1403,6 +1391,7 @@ int build_resident(Plan& p) {
     r.ytile = yt;
     r.err = p.d_err;
     r.budget = p.spin_budget;
+    if ((rc = build_resident_prep(p, w1)) != WF_OK) return rc;
     // one workgroup per compute unit, all resident at once
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_fn(p), kThreads, 0);
@@ -1412,25 +1401,14 @@ int build_resident(Plan& p) {
     return WF_OK;
 }
 
-int enqueue_resident(Plan& p, hipStream_t stream) {
+int enqueue_resident(Plan& p, const CallPtrs& c, hipStream_t stream) {
     ResArgs r = p.res;
     r.stamps = p.stamps;
     r.stamps_cap = p.stamps_cap;
     r.budget = p.spin_budget;
     r.stall = p.stall;
-    const size_t ncnt = (size_t)kResRoles * r.ntasks * kXcds;
-    hipLaunchKernelGGL(k_res_zero, dim3(1024), dim3(256), 0, stream, r.cnt, ncnt);
-    // fp32: h1 and h2 to the fill pattern their readers check for
-    if (p.precision != WF_BF16) {
-        hipLaunchKernelGGL(k_res_fill, dim3(2048), dim3(256), 0, stream, static_cast<unsigned*>(r.h1),
-                           (size_t)r.ntasks * kTile * p.Np1);
-        hipLaunchKernelGGL(k_res_fill, dim3(2048), dim3(256), 0, stream, static_cast<unsigned*>(r.h2),
-                           (size_t)r.ntasks * kTile * p.Np2);
-    }
-    if (!r.hoist) {
-        int rc = enqueue_hoist(p, stream);
-        if (rc != WF_OK) return rc;
-    }
+    int rc = enqueue_resident_prep(p, c, stream);
+    if (rc != WF_OK) return rc;
     StepArgs a = p.args;
     int T = p.T;
     void* args[] = {&a, &r, &T};

@@ -220,3 +220,32 @@ def test_consecutive_calls_with_new_inputs(driver):
         plan.sync()
         assert np.array_equal(s_out.cpu().numpy(), sym)
     plan.close()
+
+
+@pytest.mark.parametrize("name,H,W", [
+    ("minnen-16x16-m192", 15, 17),              # the hoisted product's 16-latent tiles
+    ("minnen-kodak-48x32-m192", 33, 51),        # 64 latents x 64 columns
+    ("minnen-hr-4k-240x135-m320", 61, 101),     # 128 x 192
+])
+@pytest.mark.parametrize("value", [1e12, np.inf, np.nan])
+def test_resident_hoist_outlier(name, H, W, value):
+    """The resident driver's hoisted layer-1 part runs on f16 pairs scaled by a
+    tile's largest value: an outlier or a value that is not finite in the last
+    latent (no other depends on it) must not touch the other latents of its
+    tile, and reaches its own outputs as on the graph driver."""
+    cfg, w, table, psi, sym = inputs.make_inputs(name, H=H, W=W)
+    psi = psi.copy()
+    psi[0, H - 1, W - 1, 3] = value
+    got = {}
+    for driver in ("graph", "resident"):
+        plan = wf.Plan(w, table, H, W, 1, cfg["K"], driver=driver)
+        out = plan.decode(torch.from_numpy(psi).cuda(), torch.from_numpy(sym).cuda())
+        plan.sync()
+        got[driver] = {k: v.cpu().numpy() for k, v in out.items()}
+        plan.close()
+    for k in ("y_hat", "mean", "scale"):
+        a, b = (got[d][k].reshape(H * W, -1) for d in ("graph", "resident"))
+        assert np.abs(a[:-1] - b[:-1]).max() <= 1e-4, k     # the parity bar
+        assert np.array_equal(np.isfinite(a[-1]), np.isfinite(b[-1])), k
+        f = np.isfinite(a[-1])
+        assert not f.any() or np.abs(a[-1] - b[-1])[f].max() <= 1e-4 * max(1.0, np.abs(a[-1][f]).max()), k
