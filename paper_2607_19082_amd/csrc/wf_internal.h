@@ -94,14 +94,15 @@ constexpr int kResMaxParts = 12;    // k-parts of the old-tap context (the last 
 // 32 bytes apart, or packed, 12.4-16.5 ms.
 constexpr int kResSlotWords = 64;
 constexpr unsigned kResFill = 0xFFFFFFFFu;   // fill pattern of the resident fp32 h1 and h2
-constexpr int kResRep = 2;          // replicas of every weight slice (they take alternate tasks)
+constexpr int kResPerCu = 2;        // workgroups of k_resident per compute unit
+constexpr int kResRepMin = 2, kResRepMax = 4;   // replicas of a weight slice (they take the tasks in turn)
 constexpr int kResKbaseLds = 4096;  // largest T + 1 of a resident plan (its step table sits in LDS)
 constexpr int kResMinHoist = 8;     // fewest spare workgroups that compute the hoisted layer-1 part in the launch
 constexpr int kResHoistLead = 64;   // tasks by which that part runs ahead of layer 3
 
 struct ResArgs {
     int first[kResRoles + 1];   // workgroups [first[r], first[r+1]) play role r
-    const int* per_slot;        // [kResRoles][kResRep][8]: workgroups of role r, replica h, in XCD class x
+    const int* per_slot;        // [kResRoles][kResRepMax][8]: workgroups of role r, replica h, in XCD class x
     int parts;                  // k-parts of the old-tap context: parts - 1 split the old taps before the
                                 // first one of age 2 (raster order; k-blocks [0, pre_kb)) evenly, the
                                 // last one (CTXL) holds the rest, [pre_kb, n_old M / kK)

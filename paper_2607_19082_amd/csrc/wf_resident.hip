@@ -13,7 +13,7 @@
 //   C1(g)      layer 3, the scale columns of channel tile g, scale and index
 //   H          (bf16, when enough slots are left) the hoisted layer-1 part
 //              W1 psi + b1 of one task at a time, streaming its weights
-// Each slice is held by kResRep workgroups (replicas) that take alternate
+// Each slice is held by two to four workgroups (replicas) that take alternate
 // tasks, two workgroups per compute unit.  A task of a role is one 16-row band (grid rows 16 beta .. 16 beta + 15 of
 // image b) at one wavefront step t: the band's latents on wavefront t, at
 // most one per grid row (Sec. III-A, Eq. 4: they are d-separated).  Every
@@ -210,7 +210,7 @@ __shared__ int res_kbase_lds[kResKbaseLds];
 // and the per-step band table (first band | bands per image << 16)
 __shared__ int res_steps_lds[kResKbaseLds];
 // and the per-slot workgroup counts of the roles (the waits' targets)
-__shared__ int res_per_slot_lds[kResRoles * kResRep * kXcds];
+__shared__ int res_per_slot_lds[kResRoles * kResRepMax * kXcds];
 
 __device__ __forceinline__ ResDeps res_deps(const StepArgs& a, const ResArgs& r, int role, int t, int b, int beta,
                                             int k) {
@@ -259,7 +259,7 @@ __device__ __forceinline__ bool res_wait(const ResArgs& r, ResWait w0, ResWait w
             // (one hoist workgroup per task, counting into class slot 0)
             const unsigned n =
                 w.role == RR_H ? (x == 0 ? 1u : 0u)
-                               : (unsigned)res_per_slot_lds[(w.role * kResRep + w.k % r.nrep) * kXcds + x];
+                               : (unsigned)res_per_slot_lds[(w.role * kResRepMax + w.k % r.nrep) * kXcds + x];
             tgt = n + (unsigned)r.stall;
             p = res_slot(r, w.role, w.k, x);
         }
@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int l = threadIdx.x; l < a.L; l += blockDim.x) tab[l] = a.table[l];
     for (int l = threadIdx.x; l <= T; l += blockDim.x) res_kbase_lds[l] = r.kbase[l];   // (T < kResKbaseLds)
     for (int l = threadIdx.x; l < T; l += blockDim.x) res_steps_lds[l] = r.steps[l];
-    for (int l = threadIdx.x; l < kResRoles * kResRep * kXcds; l += blockDim.x) res_per_slot_lds[l] = r.per_slot[l];
+    for (int l = threadIdx.x; l < kResRoles * kResRepMax * kXcds; l += blockDim.x) res_per_slot_lds[l] = r.per_slot[l];
     __syncthreads();
     // (selects, not a loop: a runtime index into the argument block would
     // copy it to scratch memory)
@@ -1298,42 +1298,67 @@ int build_resident(Plan& p, const float* w1) {
     if (e != hipSuccess) return fail(WF_E_HIP, std::string("device query: ") + hipGetErrorString(e));
     if (p.cu_limit > 0 && p.cu_limit < cus) cus = p.cu_limit;
     const int crit = p.Np1 / kTile + p.Np2 / kTile + 2 * G;
-    const int slots = kResRep * cus;   // two workgroups per compute unit
+    const int slots = kResPerCu * cus;   // two workgroups per compute unit
     // the fewest parts before the last whose slices fit the registers
     int np = 0;
     if (pre_kb > 0)
         for (np = 1; ceil_div(ceil_div(pre_kb, np), kWaves) > kb[0];) ++np;
     if (np + 1 > kResMaxParts) return fail(WF_E_UNSUPPORTED, "resident driver: the old-tap context needs too many parts");
-    auto need = [&](int n_) { return kResRep * (crit + ncg * n_ + ncgl); };
-    if (need(np) > slots)
-        return fail(WF_E_UNSUPPORTED, "resident driver: " + std::to_string(need(np)) + " workgroups for " +
-                                          std::to_string(slots) + " slots");
+    // Replicas of every slice.  Two, with the slots that leaves for context
+    // parts (or the in-launch hoist), are fastest while a step has few tasks;
+    // from 4.5 tasks a step (larger batches, tall grids) the roles' throughput
+    // sets the pace and more replicas win if they fit.  M = 192 fp32, 2 / 3 / 4
+    // replicas, us: 135x200, 3.6 tasks 6630 / 6830 / -; 68x120 B = 2, 4.9 tasks
+    // 4170 / 3900 / -, B = 4, 9.8 tasks 7490 / 6250 / -, mixture B = 2 8500 /
+    // 7000 / -; relaxed B = 3, 8.6 tasks 5320 / 4420 / 3640.  bf16 takes three
+    // (B = 4: 6130 / 4770 / 5050).  M = 320 has slots for two only.
+    std::vector<int> kbase, steps;
+    const long long tasks = res_kbase(p, kbase, steps);
+    int nrep = kResRepMin;
+    auto need = [&](int n_) { return nrep * (crit + ncg * n_ + ncgl); };
     // fp32: spare slots take more context parts (shorter context tasks);
     // bf16: they compute the hoisted layer-1 part in the launch (4K: 9.74 ms
     // with 68 such workgroups and the fewest parts, 9.87 with 48, 11.0 with
     // 28 and two more parts)
-    while (!bf && np > 0 && need(np + 1) <= slots && np + 2 <= kResMaxParts && pre_kb / (np + 1) >= kWaves) ++np;
-    const int parts = np + 1;
+    const int np_min = np;
+    auto spread = [&] {
+        np = np_min;
+        while (!bf && np > 0 && need(np + 1) <= slots && np + 2 <= kResMaxParts && pre_kb / (np + 1) >= kWaves) ++np;
+    };
     // a wave's old-tap k-blocks must lie in at most kResSeg taps
-    {
+    auto spans_few_taps = [&] {
         const int tapkb = M / kk;
-        for (int q = 0; q < parts; ++q) {
+        for (int q = 0; q <= np; ++q) {
             const int lo = q < np ? pre_kb * q / np : pre_kb, hi = q < np ? pre_kb * (q + 1) / np : nkb_old;
             const int per = ceil_div(hi - lo, kWaves);
             for (int wv = 0; wv < kWaves; ++wv) {
                 const int k0 = std::min(hi, lo + wv * per), k1 = std::min(hi, k0 + per);
-                if (k1 > k0 && (k1 - 1) / tapkb - k0 / tapkb + 1 > kResSeg)
-                    return fail(WF_E_UNSUPPORTED, "resident driver: a context slice spans too many taps (M too small)");
+                if (k1 > k0 && (k1 - 1) / tapkb - k0 / tapkb + 1 > kResSeg) return false;
             }
         }
-    }
+        return true;
+    };
+    if (2 * tasks >= 9LL * p.T)
+        for (nrep = bf ? 3 : kResRepMax; nrep > kResRepMin; --nrep) {
+            if (need(np_min) > slots) continue;
+            spread();
+            if (spans_few_taps()) break;
+        }
+    np = np_min;
+    if (need(np) > slots)
+        return fail(WF_E_UNSUPPORTED, "resident driver: " + std::to_string(need(np)) + " workgroups for " +
+                                          std::to_string(slots) + " slots");
+    spread();
+    const int parts = np + 1;
+    if (!spans_few_taps())
+        return fail(WF_E_UNSUPPORTED, "resident driver: a context slice spans too many taps (M too small)");
     r.parts = parts;
     r.pre_kb = pre_kb;
     r.ctx_lag = lag;
-    r.nrep = kResRep;
+    r.nrep = nrep;
     const int n[RR_H] = {ncg * np, ncgl, p.Np1 / kTile, p.Np2 / kTile, G, G};
     r.first[0] = 0;
-    for (int k = 0; k < RR_H; ++k) r.first[k + 1] = r.first[k] + kResRep * n[k];
+    for (int k = 0; k < RR_H; ++k) r.first[k + 1] = r.first[k] + nrep * n[k];
     // bf16: the slots left over compute the hoisted layer-1 part inside the
     // launch, one task each in turn (4K: 9.74 against 10.19 ms with the hoist
     // kernel before the launch).  fp32: the kernel before the launch (the
@@ -1345,15 +1370,15 @@ int build_resident(Plan& p, const float* w1) {
     r.first[kResRoles] = r.first[RR_H] + nh;
     r.hoist = nh > 0 ? 1 : 0;
     const int grid = r.first[kResRoles];
-    int per_slot[kResRoles * kResRep * kXcds] = {};
+    int per_slot[kResRoles * kResRepMax * kXcds] = {};
     for (int k = 0; k < RR_H; ++k)
         for (int g = r.first[k]; g < r.first[k + 1]; ++g) {
             const int h = (g - r.first[k]) / n[k];   // the workgroup's replica
-            ++per_slot[(k * kResRep + h) * kXcds + g % kXcds];
+            ++per_slot[(k * kResRepMax + h) * kXcds + g % kXcds];
         }
     int* d_per = nullptr;
     int rc;
-    if ((rc = res_alloc(p, &d_per, kResRoles * kResRep * kXcds)) != WF_OK) return rc;
+    if ((rc = res_alloc(p, &d_per, kResRoles * kResRepMax * kXcds)) != WF_OK) return rc;
     e = hipMemcpy(d_per, per_slot, sizeof(per_slot), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(WF_E_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
     r.per_slot = d_per;
@@ -1362,8 +1387,6 @@ int build_resident(Plan& p, const float* w1) {
     const size_t nbs = (size_t)r.nbs;
     if (p.T + 1 > kResKbaseLds)
         return fail(WF_E_UNSUPPORTED, "resident driver: more than " + std::to_string(kResKbaseLds - 1) + " wavefront steps");
-    std::vector<int> kbase, steps;
-    const long long tasks = res_kbase(p, kbase, steps);
     r.ntasks = (int)tasks;
     int *d_kbase = nullptr, *d_steps = nullptr;
     if ((rc = res_alloc(p, &d_kbase, kbase.size())) != WF_OK) return rc;
@@ -1396,7 +1419,7 @@ int build_resident(Plan& p, const float* w1) {
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_fn(p), kThreads, 0);
     if (e != hipSuccess) return fail(WF_E_HIP, std::string("occupancy query: ") + hipGetErrorString(e));
-    if (per_cu < kResRep) return fail(WF_E_UNSUPPORTED, "resident kernel: two workgroups per CU do not fit");
+    if (per_cu < kResPerCu) return fail(WF_E_UNSUPPORTED, "resident kernel: two workgroups per CU do not fit");
     p.grid = grid;
     return WF_OK;
 }

@@ -249,3 +249,30 @@ def test_resident_hoist_outlier(name, H, W, value):
         assert np.array_equal(np.isfinite(a[-1]), np.isfinite(b[-1])), k
         f = np.isfinite(a[-1])
         assert not f.any() or np.abs(a[-1] - b[-1])[f].max() <= 1e-4 * max(1.0, np.abs(a[-1][f]).max()), k
+
+
+# tasks a step, and the workgroups that then hold each weight slice: from 4.5
+# tasks three (fp32 with the relaxed mask's fewer context parts: four), below
+# it, and at M = 320, two
+@pytest.mark.parametrize("name,B,H,W,precision", [
+    ("minnen-16x16-m192", 5, 15, 17, "fp32"),                  # 5: three
+    ("minnen-16x16-m192", 4, 16, 16, "fp32"),                  # 4: two
+    ("minnen-relaxed-b8-120x68-m192", 7, 17, 19, "fp32"),      # four
+    ("cheng-gmm3-1080p-120x68-m192", 3, 33, 40, "fp32"),       # three
+    ("minnen-16x16-m192", 6, 18, 17, "bf16"),                  # three
+    ("minnen-hr-4k-240x135-m320", 5, 15, 9, "fp32"),           # 5, two
+])
+def test_resident_replicas(name, B, H, W, precision):
+    """Plans with many tasks a step hold each weight slice in more workgroups,
+    which take the tasks in turn; three calls through the same plan, each
+    against the oracle."""
+    cfg, w, table, psi, sym = make_case(name, H=H, W=W, B=B)
+    log(f"resident replicas case {name} B={B} H={H} W={W} precision={precision}")
+    ref = oracle_model(cfg, w, table, bf16=precision == "bf16").decode(psi, sym)
+    plan = gpu_plan(cfg, w, table, driver="resident", precision=precision)
+    psi_d, sym_d = torch.from_numpy(psi).cuda(), torch.from_numpy(sym).cuda()
+    for _ in range(3):
+        out = plan.decode(psi_d, sym_d)
+        plan.sync()
+        compare(to_np(out), ref, table, cfg["K"], tol=1e-4 if precision == "fp32" else 1e-3)
+    plan.close()
