@@ -48,7 +48,9 @@ CSRC = os.path.join(ROOT, "paper_2607_19082_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 # kernels of one decode call (the rest of a bench run: the floor probes, torch)
 DECODE_KERNELS = ("wf::k_phase", "wf::k_hoist", "wf::k_ctxo", "wf::k_set_call", "wf::k_persistent", "wf::k_zero_u32",
-                  "wf::k_dataflow", "wf::k_zero_u128", "wf::k_resident", "wf::k_res_zero")
+                  "wf::k_dataflow", "wf::k_zero_u128", "wf::k_resident", "wf::k_res_init", "wf::k_res_prep")
+# the first launch of every call (the resident driver's publishes the call's pointers itself)
+CALL_KERNELS = ("wf::k_set_call", "wf::k_res_init", "wf::k_res_prep")
 
 
 # kernels of the bench's per-step latency leg (one traced decode by the
@@ -115,7 +117,7 @@ def summarize_traffic(fetch_dir, write_dir, cal_fetch_dir, cal_write_dir, cal_by
     w_cal = cal_bytes / (1024.0 * total(cal_write_dir, "WRITE_SIZE", is_copy))
     is_dec = lambda k: any(x in k for x in DECODE_KERNELS) and not leg_kernel(k, driver)
     fetch_rows = _pmc_rows(fetch_dir)
-    decodes = sum(1 for k, c, v in fetch_rows if c == "FETCH_SIZE" and "k_set_call" in k) - \
+    decodes = sum(1 for k, c, v in fetch_rows if c == "FETCH_SIZE" and any(x in k for x in CALL_KERNELS)) - \
         sum(1 for k, c, v in fetch_rows if c == "FETCH_SIZE" and "wf::k_persistent" in k and leg_kernel(k, driver))
     fetch = total(fetch_dir, "FETCH_SIZE", is_dec) * 1024.0 * f_cal / decodes
     write = total(write_dir, "WRITE_SIZE", is_dec) * 1024.0 * w_cal / decodes
@@ -204,7 +206,7 @@ def summarize_stats(stats_dir, log, out, command, l_floor_us=None):
     leg = [r for r in rows if leg_kernel(r["Name"], cfg["driver"])]
     leg_calls = sum(int(r["Calls"]) for r in leg if "wf::k_persistent" in r["Name"])
     rows = [r for r in rows if r not in leg]
-    calls = sum(int(r["Calls"]) for r in rows if "k_set_call" in r["Name"]) - leg_calls
+    calls = sum(int(r["Calls"]) for r in rows if any(x in r["Name"] for x in CALL_KERNELS)) - leg_calls
     dec = sum(float(r["TotalDurationNs"]) for r in rows if any(x in r["Name"] for x in DECODE_KERNELS))
     lines = [f"# Kernel statistics: {cfg['workload']}, {cfg['precision']}, {cfg['driver']} driver"
              + (f", context approximation N = {cfg['context_approximation_group']}"
@@ -260,8 +262,10 @@ def summarize_stats(stats_dir, log, out, command, l_floor_us=None):
         lines += ["", "This run also times the transforms (`end_to_end` in the bench line): the hyper-decoder "
                   f"{e2e['hyper_decoder_ms_per_image']:.3f} ms and the synthesis {e2e['synthesis_ms_per_image']:.3f} "
                   f"ms per image ({e2e['ms_per_image']:.3f} ms end to end with the decode); their layers run as "
-                  "`k_conv<P, mode, row tiles, column tiles, column waves>` (mode 0: transposed conv by output "
-                  "class, 1: 3x3 conv, 2: inverse GDN, 3: the image layer with the classes as columns)."]
+                  "`k_conv<P, mode, row tiles, column tiles, column waves>` (hyper-decoder; mode 0: transposed conv "
+                  "by output class, 1: 3x3 conv) and `k_synth<operands, mode, row tiles, column tiles, column waves, "
+                  "inverse GDN in the epilogue>` (synthesis; mode 2: inverse GDN, 3: the image layer with the classes "
+                  "as columns)."]
     # runs that also time the rANS decode or the transforms get a summary of their own
     out = out[:-len(".md")] + ("_entropy" if ec else "") + ("_transforms" if e2e else "") + ".md"
     with open(out, "w") as f:
@@ -475,13 +479,13 @@ def trace_step_latency(trace_csv, call, T, lfloor):
     next step's (the last: to its last kernel's end), gaps included."""
     import csv
     rows = sorted(csv.DictReader(open(trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
-    calls = [i for i, r in enumerate(rows) if "wf::k_set_call" in r["Kernel_Name"]]
+    calls = [i for i, r in enumerate(rows) if any(x in r["Kernel_Name"] for x in CALL_KERNELS)]
     if call >= len(calls):
         return None
     ph = []
     for r in rows[calls[call] + 1:]:
         k = r["Kernel_Name"]
-        if "wf::k_set_call" in k:
+        if any(x in k for x in CALL_KERNELS):
             break
         if "wf::k_phase" in k:
             ph.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"])))
@@ -858,7 +862,7 @@ def main():
                      "traffic_GBps": None if traffic is None else traffic / (dec_ms * 1e-3) / 1e9,
                      "kernel": {"persistent": "k_persistent (one launch = one decode)",
                                 "dataflow": "one decode call: counter reset, hoist and one k_dataflow launch",
-                                "resident": "one decode call: counter reset, hoist and one k_resident launch",
+                                "resident": "one decode call: preparation (counters, fills, hoist) and one k_resident launch",
                                 "graph": "one replay of the decode graph (hoist, context, one k_phase per phase)",
                                 "stream": "all kernels of one decode call"}[args.driver],
                      "algorithmic_gflop_per_launch": fl / 1e9, "launch_ms_events": dec_ms,
