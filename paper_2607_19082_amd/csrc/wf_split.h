@@ -512,6 +512,9 @@ __device__ __forceinline__ void synth_tile(const SynthArgs& a, int bid) {
             bad = __syncthreads_or(low);
         }
         if (bad) {
+            // (uniform.  A chunk with a value that is not finite was left just
+            // after block_max_bits' `red` was read; the epilogue writes it again)
+            __syncthreads();
             s = 0;
             conv_tile_f32<MODE, RT, CT>(a, a.wp[cls], nk, ntap, nkx, b, qy, qx, ct0, acc);
         }

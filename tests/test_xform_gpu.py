@@ -189,3 +189,24 @@ def test_synthesis_not_finite(value, where, H, W):
         away = np.ones_like(lost)
         away[:, 16 * 2:16 * 7 + 16, 16 * 4:16 * 9 + 16] = False   # two latents around it
         check(np.where(away, got, 0), np.where(away, ref, 0), "fp32", "image away from the value")
+
+
+@pytest.mark.parametrize("H,W", [(12, 20), (24, 40)])   # inverse GDN apart; in the third layer's conv kernel
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_synthesis_not_finite_in_a_halo(value, H, W):
+    """A value that is not finite in the grid's last latent: workgroups whose
+    patch only touches it in its halo leave the f16 products too (beside the
+    next reduction of the workgroup), and every pixel out of its reach is as
+    far from the oracle as without it; three calls give the same bits."""
+    N, M = 32, 32
+    w = inputs.make_transform_weights(N, M)
+    y = np.random.default_rng(12).normal(scale=2.0, size=(1, H, W, M)).astype(np.float32)
+    ref = T.synthesis(y, w)
+    y[0, H - 1, W - 1, 7] = value
+    x = wf.Xform(w, N, M, 1, H, W, "fp32")
+    got = [x.synthesis(torch.from_numpy(y).cuda()).cpu().numpy() for _ in range(3)]
+    x.close()
+    assert all(np.array_equal(got[0], g, equal_nan=True) for g in got[1:])
+    away = np.ones_like(ref, bool)
+    away[:, 16 * (H - 3):, 16 * (W - 3):] = False   # two latents around it
+    check(np.where(away, got[0], 0), np.where(away, ref, 0), "fp32", "image away from the value")
