@@ -38,6 +38,7 @@
 namespace wf {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4u __attribute__((aligned(4)));   // one at any float of a caller's array (a store of it is still one instruction)
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 struct b8x2 {   // eight activation values as bf16 pairs
     b8 hi, lo;

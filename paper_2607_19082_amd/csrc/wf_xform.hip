@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_conv(ConvArgs a) {
             const int n = (ct0 + j) * kTile;
             f4 v = acc[i][j] + *reinterpret_cast<const f4*>(a.bias + n + kq * 4);
             if (a.relu) v = f4{fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f), fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f)};
-            *reinterpret_cast<f4*>(o + n) = v;
+            *reinterpret_cast<f4u*>(o + n) = v;      // (psi need only be aligned to 4 bytes)
         }
     }
 }

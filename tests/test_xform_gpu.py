@@ -145,6 +145,26 @@ def test_hyper_tile_edges(precision, N, M, B, H, W):
     check(got, T.hyper_synthesis(z, w)[:, :H, :W], precision, "psi")
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_hyper_unaligned(precision):
+    """z_hat and psi at any float of larger arrays: the same bits, and nothing
+    around psi written."""
+    N, M, B, H, W = 32, 64, 1, 9, 13
+    w = inputs.make_transform_weights(N, M)
+    z = torch.from_numpy(inputs.make_zhat(B, -(-H // 4), -(-W // 4), N)).cuda()
+    x = wf.Xform(w, N, M, B, H, W, precision)
+    ref = x.hyper_synthesis(z).cpu().numpy()
+    for off in (1, 2, 3):
+        zb = torch.zeros(z.numel() + off, device="cuda")
+        zb[off:] = z.reshape(-1)
+        pb = torch.full((ref.size + 8,), 7.0, device="cuda")
+        psi = pb[off:off + ref.size].view(ref.shape)
+        x.hyper_synthesis(zb[off:].view(z.shape), psi=psi)
+        assert np.array_equal(psi.cpu().numpy(), ref)
+        assert bool((pb[:off] == 7).all()) and bool((pb[off + ref.size:] == 7).all())
+    x.close()
+
+
 @pytest.mark.parametrize("H,W", [(9, 11), (27, 33)])   # inverse GDN apart; in the third layer's conv kernel
 @pytest.mark.parametrize("scale", [1e-12, 1e-3, 300.0])   # (inverse GDN squares three times: more overflows fp32)
 def test_synthesis_scales(scale, H, W):
