@@ -38,6 +38,7 @@
 namespace wf {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef f4 f4u __attribute__((aligned(4)));   // one at any float of a caller's array (a store of it is still one instruction)
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 struct b8x2 {   // eight activation values as bf16 pairs
@@ -171,6 +172,22 @@ __device__ __forceinline__ void st1(float* base, size_t idx, float v) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rsrc(base), (int)(idx * 4), 0, kSc1);
     else
         base[idx] = v;
+}
+__device__ __forceinline__ f2 ld2(const float* base, size_t idx, bool ok = true) {
+    const int off = ok ? (int)(idx * 4) : kOob;
+    return __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(rsrc(base), off, 0, 0));
+}
+__device__ __forceinline__ void st2_coh(float* base, size_t idx, f2 v) {
+    typedef __attribute__((ext_vector_type(2))) unsigned u2;
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rsrc(base), (int)(idx * 4), 0, kSc1);
+}
+template <bool COH>
+__device__ __forceinline__ void st4(float* base, size_t idx, f4 v) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u4;
+    if (COH)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rsrc(base), (int)(idx * 4), 0, kSc1);
+    else
+        *reinterpret_cast<f4*>(base + idx) = v;
 }
 template <bool COH>
 __device__ __forceinline__ void st1h(uint16_t* base, size_t idx, uint16_t h) {

@@ -84,6 +84,9 @@ enum ResRole { RR_CTX = 0, RR_CTXL = 1, RR_A = 2, RR_B = 3, RR_C0 = 4, RR_C1 = 5
 // layer 2, layer 3 (K = 1), layer 3 (K = 3), last context part (kResCtxlNc tiles)
 constexpr int kResKbF32[6] = {6, 20, 17, 14, 8, 10};
 constexpr int kResKbBf16[6] = {6, 10, 9, 7, 4, 10};
+// fp32: k-blocks of the longest context part where one wave holds a part alone
+// (res_ctx_whole): M = 192 with the relaxed and the full mask
+constexpr int kResKbWhole[2] = {7, 9};
 constexpr int kResCtxNc = 4;       // column tiles of a context part's slice (64 of the 2M columns)
 constexpr int kResCtxlNc = 2;      // column tiles of a last-part slice
 constexpr int kResMaxNc = 6;        // column tiles of one layer-3 role (K = 3: 3 logits + 3 means)
@@ -113,6 +116,8 @@ struct ResArgs {
                                 // slice q % n and runs the tasks k with k % nrep == q / n.  CTX slices are
                                 // (column tile, part 0 .. parts-2), CTXL slices the column tiles of the
                                 // last part, which adds the other parts in
+    int whole;                  // k-blocks of the longest part where a CTX slice holds four parts, one a wave
+                                // (slices are (column tile, four parts)); else 0
     int nbands;                 // 16-row bands per image (ceil(H / 16)); band slot bs = b * nbands + band
     int nbs;                    // B * nbands
     unsigned* cnt;              // [kResRoles][ntasks][8] counter slots, kResSlotWords words apart

@@ -2,7 +2,8 @@
 // Every workgroup keeps one slice of the weights in registers for the whole
 // decode and plays one fixed role:
 //   CTX(c, p)  old-tap context, column tile c of 2M, k-part p < P-1 of the
-//              old taps
+//              old taps (plans with more than two replicas may hold four
+//              parts in a workgroup, one a wave: res_ctx_whole)
 //   CTXL(c)    the same for the last part P-1, which also adds the other
 //              parts' results (so layer 1 reads one context value)
 //   A(c)       layer 1 over [new taps ; old-tap context], column tile c of Np1
@@ -13,9 +14,9 @@
 //   C1(g)      layer 3, the scale columns of channel tile g, scale and index
 //   H          (bf16, when enough slots are left) the hoisted layer-1 part
 //              W1 psi + b1 of one task at a time, streaming its weights
-// Each slice is held by two to four workgroups (replicas) that take alternate
-// tasks, two workgroups per compute unit.  A task of a role is one 16-row band (grid rows 16 beta .. 16 beta + 15 of
-// image b) at one wavefront step t: the band's latents on wavefront t, at
+// Each slice is held by two to four workgroups (replicas) that take the tasks
+// in turn, two workgroups per compute unit.  A task of a role is one 16-row
+// band (grid rows 16 beta .. 16 beta + 15 of image b) at one wavefront step t: the band's latents on wavefront t, at
 // most one per grid row (Sec. III-A, Eq. 4: they are d-separated).  Every
 // workgroup runs the tasks of its role in the same global order (steps, then
 // images, then bands), computes its 16 x 16 (x the role's column tiles)
@@ -115,7 +116,7 @@ __device__ __forceinline__ StepArgs uni_args(const StepArgs& x) {
 __device__ __forceinline__ ResArgs uni_args(const ResArgs& x) {
     ResArgs r = x;
 #define WF_U(f) r.f = uni(x.f)
-    WF_U(per_slot); WF_U(parts); WF_U(pre_kb); WF_U(ctx_lag); WF_U(nrep); WF_U(nbands); WF_U(nbs); WF_U(cnt); WF_U(kbase); WF_U(steps); WF_U(ctx); WF_U(h1); WF_U(h2);
+    WF_U(per_slot); WF_U(parts); WF_U(pre_kb); WF_U(ctx_lag); WF_U(nrep); WF_U(whole); WF_U(nbands); WF_U(nbs); WF_U(cnt); WF_U(kbase); WF_U(steps); WF_U(ctx); WF_U(h1); WF_U(h2);
     WF_U(ytile);
     WF_U(err);
     WF_U(stamps); WF_U(ntasks); WF_U(stall); WF_U(hoist);
@@ -599,11 +600,15 @@ __device__ __forceinline__ OldSrc<P> old_src(const StepArgs& a, const Row& w, co
 }
 // acc += the wave's old-tap k-blocks x its weight slice, all loads issued
 // before the first MFMA.
-template <class P, int KB, int NC>
+template <class P, int KB, int NC, bool WFIRST = false>
 __device__ __forceinline__ void wdot_old(const WSlice<P, KB, NC>& s, const void* src, OldSrc<P> os, f4 (&acc)[NC]) {
     const int n = __builtin_amdgcn_readfirstlane(s.n);
     const auto rs = rsrc(src);
     typename P::A av[KB];
+    auto mma = [&](int u, int c) {   // (WFIRST, fp32: the transposed tile, the same sums)
+        if constexpr (WFIRST) acc[c] = P::mma(s.w[u][c], av[u], acc[c]);
+        else acc[c] = P::mma(av[u], s.w[u][c], acc[c]);
+    };
     auto load = [&](int u) {
         const int off = os.at(u);
         if constexpr (P::kBf16)
@@ -620,7 +625,7 @@ __device__ __forceinline__ void wdot_old(const WSlice<P, KB, NC>& s, const void*
 #pragma unroll
         for (int u = 0; u < KB; ++u)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] = P::mma(av[u], s.w[u][c], acc[c]);
+            for (int c = 0; c < NC; ++c) mma(u, c);
         return;
     }
 #pragma unroll
@@ -630,12 +635,13 @@ __device__ __forceinline__ void wdot_old(const WSlice<P, KB, NC>& s, const void*
     for (int u = 0; u < KB; ++u)
         if (u < n)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] = P::mma(av[u], s.w[u][c], acc[c]);
+            for (int c = 0; c < NC; ++c) mma(u, c);
 }
 
-// Element offset of context part `part` of task k (16 rows x 2M, tile order).
-__device__ __forceinline__ size_t ctx_base(const StepArgs& a, const ResArgs& r, int k, int part) {
-    return ((size_t)k * r.parts + part) * kTile * 2 * a.M;
+// Context parts of task k ([parts] x (16 rows x 2M), tile order).  The task's
+// own base: all tasks' parts together may be larger than a buffer window.
+__device__ __forceinline__ float* ctx_of(const StepArgs& a, const ResArgs& r, int k) {
+    return r.ctx + (size_t)uni(k) * (unsigned)(r.parts * kTile * 2 * a.M);
 }
 
 // ---------------------------------------------------------------------------
@@ -675,12 +681,42 @@ __device__ __noinline__ void res_ctx(const StepArgs& a_in, const ResArgs& r_in, 
     for_tasks(a, T, rep, r.nrep, [&](int t, int b, int beta, int k) {
         res_stamp(r, k, 0);
         // the addresses depend on the task only: computed before the wait
-        const size_t e = ctx_base(a, r, k, 0) + tile_idx<PF32>(ro, c * NC * kTile + (lane & 15), 2 * a.M);
+        float* ctx = ctx_of(a, r, k);
+        const size_t e = tile_idx<PF32>(ro, c * NC * kTile + (lane & 15), 2 * a.M);
         const Row w = band_row(a, b, beta, t, lane & 15);
         const OldSrc<P> os = old_src<P>(a, w, ot);
         const ResDeps dp = res_deps(a, r, LAST ? RR_CTXL : RR_CTX, t, b, beta, k);
         if (!res_wait(r, dp.w[0], dp.w[1], dp.w[2], bail)) return false;
         res_stamp(r, k, 1);
+        if constexpr (LAST && !P::kBf16) {
+            // weights first: a lane holds four columns of one row, and of the
+            // NC x 64 such pieces every thread adds and stores half a one
+            // (whole lines; in the other order each load of the parts before
+            // touches 16 bytes of every line of a tile)
+            static_assert(NC * 64 * 2 == kThreads, "a thread for every half piece");
+            const int cc = threadIdx.x >> 7, l = (threadIdx.x >> 1) & 63, h = threadIdx.x & 1;
+            const size_t e2 = (size_t)(c * NC + cc) * 256 + l * 4 + h * 2;
+            f2 prev{0.0f, 0.0f};
+#pragma unroll
+            for (int p2 = 0; p2 < kResMaxParts - 1; ++p2) prev = prev + ld2(ctx, e2 + p2 * pstride, p2 < np);
+            f4 acc[NC];
+#pragma unroll
+            for (int q2 = 0; q2 < NC; ++q2) acc[q2] = zero4();
+            wdot_old<P, KB, NC, true>(s, src, os, acc);
+#pragma unroll
+            for (int q2 = 0; q2 < NC; ++q2) red[wave * NC + q2][lane] = acc[q2];
+            __syncthreads();
+            f2 v{0.0f, 0.0f};
+#pragma unroll
+            for (int w2 = 0; w2 < kWaves; ++w2) {
+                const f2 x = reinterpret_cast<const f2*>(&red[w2 * NC + cc][l])[h];
+                v = v + x;
+            }
+            st2_coh(ctx, e2 + part * pstride, v + prev);
+            res_signal(r, RR_CTXL, k);   // (its barrier: red has been read)
+            res_stamp(r, k, 2);
+            return true;
+        }
         // the other parts of these elements (the last part adds them; column
         // tile cc of the group is 256 elements of the tile order further)
         float prev[NC];
@@ -691,7 +727,7 @@ __device__ __noinline__ void res_ctx(const StepArgs& a_in, const ResArgs& r_in, 
             for (int p2 = 0; p2 < kResMaxParts - 1; ++p2)
 #pragma unroll
                 for (int cc = 0; cc < NC; ++cc)
-                    prev[cc] += ld1<false>(r.ctx, e + p2 * pstride + cc * 256, p2 < np);
+                    prev[cc] += ld1<false>(ctx, e + p2 * pstride + cc * 256, p2 < np);
         }
         f4 acc[NC];
 #pragma unroll
@@ -701,8 +737,73 @@ __device__ __noinline__ void res_ctx(const StepArgs& a_in, const ResArgs& r_in, 
         float v[NC];
         wreduce<NC>(red, acc, v);
 #pragma unroll
-        for (int cc = 0; cc < NC; ++cc) st1<true>(r.ctx, e + part * pstride + cc * 256, v[cc] + prev[cc]);
+        for (int cc = 0; cc < NC; ++cc) st1<true>(ctx, e + part * pstride + cc * 256, v[cc] + prev[cc]);
         res_signal(r, LAST ? RR_CTXL : RR_CTX, k);
+        res_stamp(r, k, 2);
+        return true;
+    });
+}
+
+// CTX(c, g), plans with more replicas than whole context parts fit: wave w of
+// a workgroup computes part 4 g + w on its own, so that a workgroup holds four
+// parts.  The sums are those of res_ctx, wave by wave and part by part, so a
+// latent's bits do not depend on the number of replicas.  Weights are the
+// first MFMA operand: a lane then holds four columns of one row, 16 bytes of
+// the tile order.  KB: the k-blocks of the longest part; parts differ by one,
+// so a part has KB - 1 or KB (the loads past it are masked: were they skipped,
+// the compiler would wait for all of a batch before its first MFMA).
+template <class P, int KB>
+__device__ __noinline__ void res_ctx_whole(const StepArgs& a_in, const ResArgs& r_in, int T, int q, int rep, int* bail) {
+    const StepArgs a = uni_args(a_in);
+    const ResArgs r = uni_args(r_in);
+    constexpr int NC = kResCtxNc;
+    const int ncg = 2 * a.M / (kTile * NC);
+    const int c = q % ncg, part = q / ncg * kWaves + wave_id();
+    const int lane = threadIdx.x & 63;
+    const int nkb = a.n_old * a.M / P::kK, np = r.parts - 1;
+    WSlice<P, KB, NC> s;
+    s.kb0 = part < np ? r.pre_kb * part / np : r.pre_kb;
+    s.n = part < np ? r.pre_kb * (part + 1) / np - s.kb0 : 0;
+    s.load(a.wp_old, nkb, c * NC, 1);
+    const int n = __builtin_amdgcn_readfirstlane(s.n), per = (n + kWaves - 1) / kWaves;   // (res_ctx's share of a wave)
+    const void* src = uni(a.cp->y_hat);
+    const OldTaps ot = old_taps<P>(a, __builtin_amdgcn_readfirstlane(s.kb0));
+    __builtin_amdgcn_s_waitcnt(0);   // (as in res_ctx)
+    for_tasks(a, T, rep, r.nrep, [&](int t, int b, int beta, int k) {
+        res_stamp(r, k, 0);
+        float* ctx = ctx_of(a, r, k) + (size_t)part * kTile * 2 * a.M;
+        const size_t e = (size_t)c * NC * 256 + lane * 4;
+        const Row w = band_row(a, b, beta, t, lane & 15);
+        const OldSrc<P> os = old_src<P>(a, w, ot);
+        const ResDeps dp = res_deps(a, r, RR_CTX, t, b, beta, k);
+        if (!res_wait(r, dp.w[0], dp.w[1], dp.w[2], bail)) return false;
+        res_stamp(r, k, 1);
+        if (n > 0) {
+            const auto rs = rsrc(src);
+            f4 av[KB], acc[NC], sum[NC];
+#pragma unroll
+            for (int u = 0; u < KB; ++u)
+                av[u] = __builtin_bit_cast(
+                    f4, __builtin_amdgcn_raw_buffer_load_b128(rs, u < KB - 1 || u < n ? os.at(u) : kOob, 0, 0));
+            __builtin_amdgcn_sched_barrier(0);   // (all loads in flight before the first MFMA)
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) acc[cc] = sum[cc] = zero4();
+#pragma unroll
+            for (int u = 0; u < KB; ++u) {
+                if (u && (u == per || u == 2 * per || u == 3 * per))
+#pragma unroll
+                    for (int cc = 0; cc < NC; ++cc) {
+                        sum[cc] = sum[cc] + acc[cc];
+                        acc[cc] = zero4();
+                    }
+                if (u < KB - 1 || u < n)
+#pragma unroll
+                    for (int cc = 0; cc < NC; ++cc) acc[cc] = P::mma(s.w[u][cc], av[u], acc[cc]);
+            }
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) st4<true>(ctx, e + cc * 256, sum[cc] + acc[cc]);
+        }
+        res_signal(r, RR_CTX, k);
         res_stamp(r, k, 2);
         return true;
     });
@@ -790,7 +891,8 @@ __device__ __noinline__ void res_l1(const StepArgs& a_in, const ResArgs& r_in, i
             const int hn = __builtin_amdgcn_readfirstlane(s.n), hk0 = __builtin_amdgcn_readfirstlane(s.kb0);
             const int ntap = hk0 >= tapkb;
             const size_t en = (ntap ? ns.base[1] : ns.base[0]) + (size_t)(hk0 - ntap * tapkb) * 256 + kq * 64;
-            const size_t ec = ctx_base(a, r, k, r.parts - 1) + (size_t)hk0 * 256 + lane * 4;
+            const float* ctx = ctx_of(a, r, k) + (size_t)(r.parts - 1) * kTile * 2 * M;   // (the last part's buffer holds the sum)
+            const size_t ec = (size_t)hk0 * 256 + lane * 4;
             const int offn = (ntap ? ns.ok[1] : ns.ok[0]) ? (int)(en * 4) : kBufBytes;   // (past the window: zeros)
             const int offc = w.valid ? (int)(ec * 4) : kBufBytes;
             const ResWait none{0, -1};
@@ -814,7 +916,7 @@ __device__ __noinline__ void res_l1(const StepArgs& a_in, const ResArgs& r_in, i
                 }
             };
             if (!res_wait(r, dp.w[0], none, none, bail)) return false;
-            half(rsrc(r.ctx), offc, KH);
+            half(rsrc(ctx), offc, KH);
             if (!res_wait(r, none, dp.w[1], dp.w[2], bail)) return false;
             res_stamp(r, k, 1);
             half(rsrc(r.ytile), offn, 0);
@@ -853,12 +955,12 @@ __device__ __noinline__ void res_l1(const StepArgs& a_in, const ResArgs& r_in, i
                 // the old-tap context (the last part's buffer holds the sum):
                 // eight fp32 values per k-block, loaded first, split into
                 // bf16 pairs afterwards
-                const size_t e = ctx_base(a, r, k, r.parts - 1);
+                const float* ctx = ctx_of(a, r, k) + (size_t)(r.parts - 1) * kTile * 2 * M;
                 f4 raw[ResKb<P>::a][2];
                 auto load = [&](int u) {
                     const int c0 = (skb0 + u - kbn) * 32 + kq * 8;
-                    raw[u][0] = ld4<false>(r.ctx, e + tile_idx<PF32>(lane & 15, c0, 2 * M), w.valid);
-                    raw[u][1] = ld4<false>(r.ctx, e + tile_idx<PF32>(lane & 15, c0 + 4, 2 * M), w.valid);
+                    raw[u][0] = ld4<false>(ctx, tile_idx<PF32>(lane & 15, c0, 2 * M), w.valid);
+                    raw[u][1] = ld4<false>(ctx, tile_idx<PF32>(lane & 15, c0 + 4, 2 * M), w.valid);
                 };
                 if (sn == ResKb<P>::a) {   // a full share: each MFMA waits only for its own loads
 #pragma unroll
@@ -1197,6 +1299,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (role == RR_A) __builtin_amdgcn_s_setprio(2);
     switch (role) {
     case RR_CTX:
+        if constexpr (!P::kBf16)
+            if (r.whole) {
+                if (r.whole == kResKbWhole[0]) res_ctx_whole<P, kResKbWhole[0]>(a, r, T, sl, rep, &bail);
+                else res_ctx_whole<P, kResKbWhole[1]>(a, r, T, sl, rep, &bail);
+                break;
+            }
         res_ctx<P, false>(a, r, T, sl, rep, red, &bail);
         break;
     case RR_CTXL:
@@ -1341,59 +1449,67 @@ int build_resident(Plan& p, const float* w1) {
     if (pre_kb > 0)
         for (np = 1; ceil_div(ceil_div(pre_kb, np), kWaves) > kb[0];) ++np;
     if (np + 1 > kResMaxParts) return fail(WF_E_UNSUPPORTED, "resident driver: the old-tap context needs too many parts");
-    // Replicas of every slice.  Two, with the slots that leaves for context
-    // parts (or the in-launch hoist), are fastest while a step has few tasks;
-    // from 4.5 tasks a step (larger batches, tall grids) the roles' throughput
-    // sets the pace and more replicas win if they fit.  M = 192 fp32, 2 / 3 / 4
-    // replicas, us: 135x200, 3.6 tasks 6630 / 6830 / -; 68x120 B = 2, 4.9 tasks
-    // 4170 / 3900 / -, B = 4, 9.8 tasks 7490 / 6250 / -, mixture B = 2 8500 /
-    // 7000 / -; relaxed B = 3, 8.6 tasks 5320 / 4420 / 3640.  bf16 takes three
-    // (B = 4: 6130 / 4770 / 5050).  M = 320 has slots for two only.
-    std::vector<int> kbase, steps;
-    const long long tasks = res_kbase(p, kbase, steps);
-    int nrep = kResRepMin;
-    auto need = [&](int n_) { return nrep * (crit + ncg * n_ + ncgl); };
+    // Two replicas of every slice.
     // fp32: spare slots take more context parts (shorter context tasks);
     // bf16: they compute the hoisted layer-1 part in the launch (4K: 9.74 ms
     // with 68 such workgroups and the fewest parts, 9.87 with 48, 11.0 with
-    // 28 and two more parts)
-    const int np_min = np;
-    auto spread = [&] {
-        np = np_min;
-        while (!bf && np > 0 && need(np + 1) <= slots && np + 2 <= kResMaxParts && pre_kb / (np + 1) >= kWaves) ++np;
-    };
-    // a wave's old-tap k-blocks must lie in at most kResSeg taps
-    auto spans_few_taps = [&] {
-        const int tapkb = M / kk;
-        for (int q = 0; q <= np; ++q) {
-            const int lo = q < np ? pre_kb * q / np : pre_kb, hi = q < np ? pre_kb * (q + 1) / np : nkb_old;
-            const int per = ceil_div(hi - lo, kWaves);
-            for (int wv = 0; wv < kWaves; ++wv) {
-                const int k0 = std::min(hi, lo + wv * per), k1 = std::min(hi, k0 + per);
-                if (k1 > k0 && (k1 - 1) / tapkb - k0 / tapkb + 1 > kResSeg) return false;
-            }
-        }
-        return true;
-    };
-    if (2 * tasks >= 9LL * p.T)
-        for (nrep = bf ? 3 : kResRepMax; nrep > kResRepMin; --nrep) {
-            if (need(np_min) > slots) continue;
-            spread();
-            if (spans_few_taps()) break;
-        }
-    np = np_min;
+    // 28 and two more parts).  The parts are the groups that the context's
+    // sums are added in: they follow from the model, the mask and the device
+    // alone, never from the grid or the batch, so that an image's bits are the
+    // same alone, in a batch and beside other latents.
+    int nrep = kResRepMin;
+    auto need = [&](int n_) { return nrep * (crit + ncg * n_ + ncgl); };
     if (need(np) > slots)
         return fail(WF_E_UNSUPPORTED, "resident driver: " + std::to_string(need(np)) + " workgroups for " +
                                           std::to_string(slots) + " slots");
-    spread();
+    while (!bf && np > 0 && need(np + 1) <= slots && np + 2 <= kResMaxParts && pre_kb / (np + 1) >= kWaves) ++np;
     const int parts = np + 1;
-    if (!spans_few_taps())
-        return fail(WF_E_UNSUPPORTED, "resident driver: a context slice spans too many taps (M too small)");
+    // a wave's old-tap k-blocks must lie in at most kResSeg taps
+    const int tapkb = M / kk;
+    auto taps_of = [&](int k0, int k1) { return k1 > k0 ? (k1 - 1) / tapkb - k0 / tapkb + 1 : 0; };
+    bool whole_fits = !bf && np > 0;   // a part in one wave (see res_ctx_whole)
+    int kb_whole = 0;
+    for (int q = 0; q < parts; ++q) {
+        const int lo = q < np ? pre_kb * q / np : pre_kb, hi = q < np ? pre_kb * (q + 1) / np : nkb_old;
+        const int per = ceil_div(hi - lo, kWaves);
+        for (int wv = 0; wv < kWaves; ++wv) {
+            const int k0 = std::min(hi, lo + wv * per), k1 = std::min(hi, k0 + per);
+            if (taps_of(k0, k1) > kResSeg)
+                return fail(WF_E_UNSUPPORTED, "resident driver: a context slice spans too many taps (M too small)");
+        }
+        if (q < np) kb_whole = std::max(kb_whole, hi - lo);
+        if (q < np && taps_of(lo, hi) > kResSeg) whole_fits = false;
+    }
+    whole_fits = whole_fits && (kb_whole == kResKbWhole[0] || kb_whole == kResKbWhole[1]);
+    // More replicas from 3.5 (bf16 4.5) tasks a step (larger batches, tall
+    // grids), where the roles' throughput sets the pace, if they fit, the
+    // parts four to a workgroup if need be.  M = 192, us with 2 / 3 / 4
+    // replicas.  fp32: 2.5 tasks (120x68) 3261 / 3327 / 3311, 3.6 (200x135)
+    // 6478 / 6500 / 6486, 4.0 (two 90x60) 3028 / 2911 / 2916, 4.9 (two 120x68)
+    // 4092 / 3687 / 3622; mixture, 4.0 (240x135) 12430 / 10596 / 9648;
+    // relaxed, 5.7 (two 120x68) 3516 / 3016 / 2923; four 120x68 (9.8) 7.68 ms
+    // with two and 5.05 now, eight relaxed (22.9) 14.05 and 7.94.  bf16: 3.6
+    // tasks 5816 / 6079 / 6041, 4.9 3566 / 3361 / 3350, 9.8 6269 / 4828 / 5057,
+    // 22.9 (relaxed) 11517 / 8409 / 8852: three.  M = 320 has slots for two.
+    std::vector<int> kbase, steps;
+    const long long tasks = res_kbase(p, kbase, steps);
+    int nctx = np;   // context slices of a column group
+    if (2 * tasks >= (bf ? 9LL : 7LL) * p.T)
+        for (int m = bf ? 3 : kResRepMax; m > kResRepMin; --m) {
+            nrep = m;
+            nctx = np;
+            if (need(nctx) <= slots) break;
+            nctx = ceil_div(np, kWaves);
+            if (whole_fits && need(nctx) <= slots) break;
+            nrep = kResRepMin;
+            nctx = np;
+        }
+    r.whole = nctx < np ? kb_whole : 0;
     r.parts = parts;
     r.pre_kb = pre_kb;
     r.ctx_lag = lag;
     r.nrep = nrep;
-    const int n[RR_H] = {ncg * np, ncgl, p.Np1 / kTile, p.Np2 / kTile, G, G};
+    const int n[RR_H] = {ncg * nctx, ncgl, p.Np1 / kTile, p.Np2 / kTile, G, G};
     r.first[0] = 0;
     for (int k = 0; k < RR_H; ++k) r.first[k + 1] = r.first[k] + nrep * n[k];
     // bf16: the slots left over compute the hoisted layer-1 part inside the
@@ -1436,10 +1552,10 @@ int build_resident(Plan& p, const float* w1) {
     r.steps = d_steps;
     if ((rc = res_alloc(p, &r.cnt, (size_t)kResRoles * tasks * kXcds * kResSlotWords)) != WF_OK) return rc;
     // one output buffer per task (no address is written twice in a call);
-    // each is read through raw buffer loads and must fit their window
+    // h1 and h2 are read through raw buffer loads and must fit their window
     const size_t nt = (size_t)tasks;
     const size_t ctx_n = nt * parts * kTile * 2 * M, h1_n = nt * kTile * p.Np1, h2_n = nt * kTile * p.Np2;
-    if (std::max(ctx_n, std::max(h1_n, h2_n)) * 4 >= (size_t)kBufBytes)
+    if (std::max(h1_n, h2_n) * 4 >= (size_t)kBufBytes)
         return fail(WF_E_UNSUPPORTED, "resident driver: per-task buffers exceed the 2 GiB buffer window");
     if ((rc = res_alloc(p, &r.ctx, ctx_n)) != WF_OK) return rc;
     float *h1 = nullptr, *h2 = nullptr, *yt = nullptr;
@@ -1452,7 +1568,7 @@ int build_resident(Plan& p, const float* w1) {
     r.err = p.d_err;
     r.budget = p.spin_budget;
     if ((rc = build_resident_prep(p, w1)) != WF_OK) return rc;
-    // one workgroup per compute unit, all resident at once
+    // two workgroups per compute unit, all resident at once
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_fn(p), kThreads, 0);
     if (e != hipSuccess) return fail(WF_E_HIP, std::string("occupancy query: ") + hipGetErrorString(e));

@@ -251,18 +251,31 @@ def test_resident_hoist_outlier(name, H, W, value):
         assert not f.any() or np.abs(a[-1] - b[-1])[f].max() <= 1e-4 * max(1.0, np.abs(a[-1][f]).max()), k
 
 
-# tasks a step, and the workgroups that then hold each weight slice: from 4.5
-# tasks three (fp32 with the relaxed mask's fewer context parts: four), below
-# it, and at M = 320, two
-@pytest.mark.parametrize("name,B,H,W,precision", [
-    ("minnen-16x16-m192", 5, 15, 17, "fp32"),                  # 5: three
-    ("minnen-16x16-m192", 4, 16, 16, "fp32"),                  # 4: two
-    ("minnen-relaxed-b8-120x68-m192", 7, 17, 19, "fp32"),      # four
-    ("cheng-gmm3-1080p-120x68-m192", 3, 33, 40, "fp32"),       # three
-    ("minnen-16x16-m192", 6, 18, 17, "bf16"),                  # three
-    ("minnen-hr-4k-240x135-m320", 5, 15, 9, "fp32"),           # 5, two
+def resident_grid(M, K, relaxed, nrep, parts, whole):
+    """Workgroups of a resident fp32 plan with `parts` context parts (the last
+    one included): per replica the column tiles of layers 1 and 2, two layer-3
+    halves of each channel tile, the last context part and the other parts,
+    four to a workgroup with `whole`."""
+    tiles = lambda n: -(-n // 16)
+    d1, d2, _ = inputs.widths(M, K)
+    before = -(-(parts - 1) // 4) if whole else parts - 1
+    return nrep * (tiles(d1) + tiles(d2) + 2 * tiles(M) + 2 * M // 64 * before + 2 * M // 32)
+
+
+# tasks a step, and the workgroups that then hold each weight slice: from 3.5
+# tasks four (bf16 from 4.5 three), below it, and at M = 320, two.  fp32 with M = 192
+# keeps its 12 context parts (M = 128: 12), four to a workgroup where four
+# replicas of them would not fit otherwise.
+@pytest.mark.parametrize("name,B,H,W,precision,grid", [
+    ("minnen-16x16-m192", 5, 15, 17, "fp32", (4, 12, True)),               # 5 tasks
+    ("minnen-16x16-m192", 4, 16, 16, "fp32", (4, 12, True)),               # 4
+    ("minnen-16x16-m192", 3, 16, 16, "fp32", (2, 12, False)),              # 3
+    ("minnen-relaxed-b8-120x68-m192", 7, 17, 19, "fp32", (4, 12, True)),
+    ("cheng-gmm3-1080p-120x68-m192", 3, 33, 40, "fp32", (4, 12, True)),
+    ("minnen-16x16-m192", 6, 18, 17, "bf16", None),                        # three
+    ("minnen-hr-4k-240x135-m320", 5, 15, 9, "fp32", (2, 8, False)),        # 5, two
 ])
-def test_resident_replicas(name, B, H, W, precision):
+def test_resident_replicas(name, B, H, W, precision, grid):
     """Plans with many tasks a step hold each weight slice in more workgroups,
     which take the tasks in turn; three calls through the same plan, each
     against the oracle."""
@@ -270,9 +283,77 @@ def test_resident_replicas(name, B, H, W, precision):
     log(f"resident replicas case {name} B={B} H={H} W={W} precision={precision}")
     ref = oracle_model(cfg, w, table, bf16=precision == "bf16").decode(psi, sym)
     plan = gpu_plan(cfg, w, table, driver="resident", precision=precision)
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    if slots == 512:
+        got = plan.trace(None)[1]
+        if grid is not None:
+            assert got == resident_grid(cfg["M"], cfg["K"], cfg["relaxed"], *grid)
+        else:   # bf16: 3 x (40 + 32 + 24 column and channel tiles, 24 + 12 context slices); the rest hoists
+            assert 3 * 132 <= got <= slots
     psi_d, sym_d = torch.from_numpy(psi).cuda(), torch.from_numpy(sym).cuda()
     for _ in range(3):
         out = plan.decode(psi_d, sym_d)
         plan.sync()
         compare(to_np(out), ref, table, cfg["K"], tol=1e-4 if precision == "fp32" else 1e-3)
+    plan.close()
+
+
+@pytest.mark.parametrize("name,B,H,W,precision,M", [
+    ("minnen-16x16-m192", 5, 15, 17, "fp32", 192),                # four replicas, context parts of 8 and 9 k-blocks
+    ("minnen-relaxed-b8-120x68-m192", 7, 17, 19, "fp32", 192),    # 6 and 7
+    ("cheng-gmm3-1080p-120x68-m192", 3, 33, 40, "fp32", 192),
+    ("minnen-16x16-m192", 6, 33, 20, "fp32", 128),                # four replicas, parts split over four waves
+    ("minnen-16x16-m192", 6, 33, 20, "fp32", 64),
+    ("minnen-hr-4k-240x135-m320", 5, 17, 9, "fp32", 320),
+    ("minnen-16x16-m192", 6, 18, 17, "bf16", 192),
+])
+def test_resident_bits_alone_and_in_a_batch(name, B, H, W, precision, M):
+    """An image's bits are the same in a batch, alone, beside other images and
+    on a grid that goes on below it: a batch coded with the scale indices of
+    one plan can be decoded image by image with another."""
+    cfg = dict(inputs.workload(name), M=M)
+    K, mask = cfg["K"], "relaxed" if cfg["relaxed"] else "full"
+    w, table = inputs.make_weights(M, K), inputs.scale_table()
+    psi = inputs.make_psi(B, H, W, M)
+    psi = np.round(psi * 64) / 64                                  # (exact in any of the hoisted product's scales)
+    psi = torch.from_numpy(psi.astype(np.float32)).cuda()
+    sym = torch.from_numpy(inputs.make_symbols(B, H, W, M, cfg["lap_b"], cfg["clip"])).cuda()
+
+    def call(p, s):
+        plan = wf.Plan(w, table, p.shape[1], p.shape[2], p.shape[0], K, mask=mask, precision=precision, driver="resident")
+        out = to_np(plan.decode(p.contiguous(), s.contiguous()))
+        plan.sync()
+        plan.close()
+        return out
+
+    batch = call(psi, sym)
+    for b in (0, B - 1):
+        one = call(psi[b:b + 1], sym[b:b + 1])
+        for k in one:
+            assert np.array_equal(one[k][0], batch[k][b]), (b, k)
+    top = call(psi[:2, :H - 2], sym[:2, :H - 2])
+    for k in top:
+        assert np.array_equal(top[k], batch[k][:2, :H - 2]), k
+
+
+def test_resident_batch_past_a_window():
+    """A batch whose context parts together exceed one 2 GiB buffer window."""
+    name, B = "minnen-relaxed-b8-120x68-m192", 11                  # 8033 tasks of 288 KiB
+    cfg = inputs.workload(name)
+    H, W, M = cfg["H"], cfg["W"], cfg["M"]
+    w, table = inputs.make_weights(M, 1), inputs.scale_table()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(21)
+    psi = torch.round(64 * torch.randn((B, H, W, 2 * M), generator=g, device="cuda")) / 64
+    sym = torch.round(2 * torch.randn((B, H, W, M), generator=g, device="cuda")).int()
+    plan = wf.Plan(w, table, H, W, B, 1, mask="relaxed", driver="resident")
+    out = plan.decode(psi, sym)
+    plan.sync()
+    plan.close()
+    plan = wf.Plan(w, table, H, W, 1, 1, mask="relaxed", driver="resident")
+    for b in (0, 7, B - 1):
+        one = plan.decode(psi[b:b + 1].contiguous(), sym[b:b + 1].contiguous())
+        plan.sync()
+        for k in one:
+            assert torch.equal(one[k][0], out[k][b]), (b, k)
     plan.close()
