@@ -268,9 +268,6 @@ struct Plan {
     DfArgs df{};
     // resident driver
     ResArgs res{};
-    const void* wp_split = nullptr;      // fp32: W1[:, :2M] as f16 pairs (wf_split.h), its columns' scale
-    const int* ce_split = nullptr;       // exponents, and whether a weight is not finite
-    int force_split = 0;
     // graph driver
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -320,13 +317,11 @@ int dataflow_deps(Plan& p, std::vector<int32_t>& out);
 int enqueue_dataflow(Plan& p, hipStream_t stream);
 const void* dataflow_fn(const Plan& p);
 // Resident driver: roles and buffers of the plan, and one call.
-// (w1: the layer-1 weights, host)
-int build_resident(Plan& p, const float* w1);
+int build_resident(Plan& p);
 // Tasks and waits of a plan's geometry, flattened (host only; wf_plan_deps).
 int resident_deps(const Plan& p, std::vector<int32_t>& out);
-// Its weights for, and the launch of, what precedes k_resident (wf_prep.hip):
-// the call's pointers, counters and fills, fp32: the hoisted part.
-int build_resident_prep(Plan& p, const float* w1);
+// The launch of what precedes k_resident (wf_prep.hip): the call's pointers,
+// counters and fills, fp32: the hoisted part.
 int enqueue_resident_prep(Plan& p, const CallPtrs& c, hipStream_t stream);
 int enqueue_resident(Plan& p, const CallPtrs& c, hipStream_t stream);
 // Grid of a cooperative kernel: two workgroups per CU when they fit, else one.

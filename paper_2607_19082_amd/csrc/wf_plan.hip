@@ -438,7 +438,7 @@ static int build_plan(const wf_desc* d, Plan* p, bool geometry_only = false) {
         p->df.ncrit = p->grid >= 2 * kXcds ? p->grid / 2 / kXcds * kXcds : p->grid;
         if (p->df.ncrit == p->grid) return fail(WF_E_UNSUPPORTED, "dataflow driver needs at least 16 workgroups");
     }
-    if (p->driver == WF_DRIVER_RESIDENT && (rc = build_resident(*p, d->w1)) != WF_OK) return rc;
+    if (p->driver == WF_DRIVER_RESIDENT && (rc = build_resident(*p)) != WF_OK) return rc;
     if (d->entropy_coder == WF_EC_RANS && (rc = build_ec(p, d->scale_table, d->L)) != WF_OK) return rc;
     WF_HIP(hipDeviceSynchronize());
 

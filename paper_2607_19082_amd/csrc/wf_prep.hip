@@ -4,7 +4,7 @@
 // roles are the largest, took 5.38 ms instead of 5.29).
 #include <algorithm>
 
-#include "wf_split.h"
+#include "wf_conv.h"
 
 namespace wf {
 
@@ -32,56 +32,28 @@ __device__ __forceinline__ void res_prep(const ResPrep& p, int b, int nb) {
 __global__ __launch_bounds__(kThreads) void k_res_init(ResPrep p) { res_prep(p, blockIdx.x, gridDim.x); }
 
 // The same in the first `np` workgroups, and the hoisted part
-// P1 = b_hoist + W1[:, :2M] . psi in the others, as a product of f16 pairs
-// (wf_split.h).  The fill is bound by memory and the product by the matrix
-// cores, so they run side by side.  From the call's first launch to
-// k_resident, before (fp32 MFMA, five launches) and now: 4K 680 us (the hoist
-// 609) and 235, 16x16 88 us (the hoist 58 on 16 workgroups) and 26, of which
-// 11 are the cooperative launch's own.
-template <int RT, int CT>
-__global__ __launch_bounds__(kThreads, 2) void k_res_prep(ResPrep p, SynthArgs a, int np) {
+// P1 = b_hoist + W1[:, :2M] . psi in the others (wf_conv.h: each sum in the
+// order of the other drivers' hoist, so a latent's bits depend neither on the
+// grid nor on the latents beside it).  The fill is bound by memory and the
+// product by the matrix cores, so they run side by side: 455 us at 4K (fp32
+// MFMA: 44.5 GFLOP, 97 TFLOP/s with the fill's 0.3 GB beside them), where five
+// launches took 680, the hoist 609 of it.
+template <int RT>
+__global__ __launch_bounds__(kThreads, 2) void k_res_prep(ResPrep p, ConvArgs a, int np) {
     if ((int)blockIdx.x < np) {
         res_prep(p, blockIdx.x, np);
         return;
     }
-    synth_tile<SF16, XM_GEMM, RT, CT, 4, false>(a, blockIdx.x - np);
+    conv_tile<PF32, XM_GEMM, RT, 1, 4>(a, blockIdx.x - np, 0);
 }
 
-template <class T>
-static int prep_alloc(Plan& p, T** dst, const std::vector<T>& v) {
-    hipError_t e = hipMalloc((void**)dst, v.size() * sizeof(T));
-    if (e != hipSuccess) return fail(WF_E_NOMEM, std::string("resident driver weights: ") + hipGetErrorString(e));
-    p.owned.push_back((void*)*dst);
-    e = hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
-    return e == hipSuccess ? WF_OK : fail(WF_E_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
-}
-
-int build_resident_prep(Plan& p, const float* w1) {
-    if (p.precision == WF_BF16) return WF_OK;
-    // the hoisted part's weights as f16 pairs
-    const int M = p.M;
-    std::vector<int> ce;
-    std::vector<uint16_t> v[4];
-    p.force_split = pack_split(false, 1, 2 * M, p.d1, p.Np1, [](int, int& nkx) { return nkx = 1; },
-                               [&](int, int, int, int k, int n) { return w1[(size_t)n * 4 * M + k]; }, ce, v);
-    uint16_t* wp = nullptr;
-    int* dce = nullptr;
-    int rc = prep_alloc(p, &wp, v[0]);
-    if (rc == WF_OK) rc = prep_alloc(p, &dce, ce);
-    p.wp_split = wp;
-    p.ce_split = dce;
-    return rc;
-}
-
-template <int RT, int CT>
-static void launch_prep(const ResPrep& q, SynthArgs a, int np, hipStream_t stream) {
-    using S = SynthShape<XM_GEMM, RT, CT, 4>;
-    a.twl = RT == 1 ? 4 : (RT == 4 ? 6 : 7);
-    a.ntx = ceil_div(a.Wi, S::kPx);
-    a.nty = 1;
+template <int RT>
+static void launch_prep(const ResPrep& q, ConvArgs a, int np, hipStream_t stream) {
+    using S = ConvShape<RT, 1, 4>;
+    a.nrb = ceil_div(a.Wq, S::kPx);
     a.ncb = ceil_div(a.Cop, S::kCols);
-    const int nh = kXcds * ceil_div(a.ntx, kXcds) * a.ncb;
-    hipLaunchKernelGGL((k_res_prep<RT, CT>), dim3(np + nh), dim3(kThreads), 0, stream, q, a, np);
+    const int nh = kXcds * ceil_div(a.nrb, kXcds) * a.ncb;
+    hipLaunchKernelGGL(k_res_prep<RT>, dim3(np + nh), dim3(kThreads), 0, stream, q, a, np);
 }
 
 int enqueue_resident_prep(Plan& p, const CallPtrs& c, hipStream_t stream) {
@@ -107,16 +79,22 @@ int enqueue_resident_prep(Plan& p, const CallPtrs& c, hipStream_t stream) {
             if (rc != WF_OK) return rc;
         }
     } else {
-        SynthArgs a{};
-        a.in = c.psi; a.out = p.args.p1; a.wp[0] = p.wp_split; a.ce = p.ce_split; a.bias = p.args.b_hoist;
-        a.force_f32 = p.force_split;
-        a.B = a.Hi = a.Ho = a.ncls = 1;
-        a.Wi = a.Wo = p.B * p.H * p.W;
-        a.Ci = 2 * p.M; a.nch = ceil_div(a.Ci, 32); a.Co = a.Cop = p.Np1;
-        // 128 latents x 192 columns where that gives every compute unit work, else smaller tiles
-        if ((long long)a.Wi * a.Cop >= 256LL * 128 * 192) launch_prep<8, 3>(q, a, np, stream);
-        else if ((long long)a.Wi * a.Cop >= 256LL * 64 * 64) launch_prep<4, 1>(q, a, np, stream);
-        else launch_prep<1, 1>(q, a, np, stream);
+        ConvArgs a{};
+        a.in = c.psi; a.out = p.args.p1; a.wp[0] = p.args.wp_hoist; a.bias = p.args.b_hoist;
+        a.B = a.Hi = a.Hq = a.Ho = 1;
+        a.Wi = a.Wq = a.Wo = p.B * p.H * p.W;
+        a.Ci = 2 * p.M; a.Co = a.Cop = p.Np1;
+        // Latents of a workgroup (16 RT, by 64 columns) by the size of the
+        // product, so that small grids still spread over the chip.  us per
+        // decode with 16 / 32 / 64 / 128: 16x16 (0.16 M outputs) 599 / 603 /
+        // 606 / 616, 48x32 (0.98 M) 1343 / 1341 / 1343 / 1348, 80x48 (2.5 M)
+        // 2124 / 2118 / 2120 / 2128, 120x68 mixture (5.2 M) 4766 / 4762 /
+        // 4751 / 4752, 4K (34.7 M) 9678 / 9614 / 9536 / 9522.  (4K with 128
+        // columns: 9523 with 128 latents, 9563 with 64.)
+        const long long outputs = (long long)a.Wq * a.Cop;
+        if (outputs < 500000) launch_prep<1>(q, a, np, stream);
+        else if (outputs < 4000000) launch_prep<2>(q, a, np, stream);
+        else launch_prep<8>(q, a, np, stream);
     }
     return WF_OK;
 }

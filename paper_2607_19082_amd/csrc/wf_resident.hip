@@ -1416,7 +1416,7 @@ int resident_deps(const Plan& p, std::vector<int32_t>& out) {
     return WF_OK;
 }
 
-int build_resident(Plan& p, const float* w1) {
+int build_resident(Plan& p) {
     const StepArgs& a = p.args;
     ResArgs& r = p.res;
     const bool bf = p.precision == WF_BF16;
@@ -1567,7 +1567,6 @@ int build_resident(Plan& p, const float* w1) {
     r.ytile = yt;
     r.err = p.d_err;
     r.budget = p.spin_budget;
-    if ((rc = build_resident_prep(p, w1)) != WF_OK) return rc;
     // two workgroups per compute unit, all resident at once
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_fn(p), kThreads, 0);

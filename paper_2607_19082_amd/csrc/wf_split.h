@@ -3,14 +3,11 @@
 // plain product that hoists the hyperprior half of layer 1.
 #pragma once
 
+#include "wf_conv.h"
 #include "wf_device.h"
 #include "wf_pack.h"
 
 namespace wf {
-
-// What a tile computes: transposed conv 5x5 s2, conv 3x3 (not here), inverse
-// GDN, transposed conv with the classes as columns, plain product.
-enum { XM_DECONV = 0, XM_CONV3 = 1, XM_GDN = 2, XM_DECONV4 = 3, XM_GEMM = 4 };
 
 // ---- the synthesis transform's layers ----------------------------------------
 //
