@@ -70,10 +70,8 @@ typedef enum {
  * hi = bf16(x), lo = bf16(x - hi), about 2^-17 relative, so the weights are
  * the only coarse rounding.  Needs M a multiple of 32. */
 typedef enum {
-    WF_FP32 = 0,            /* fp32 operands, fp32 accumulate; wf_synthesis holds the
-                               operands as scaled pairs of f16 values (22-23 of fp32's 24
-                               bits, the results no further from 64 bits than with fp32
-                               products)                                                 */
+    WF_FP32 = 0,            /* fp32 operands, fp32 accumulate (wf_synthesis multiplies the
+                               operands as exact sums of three bf16 values, all 24 bits) */
     WF_BF16 = 1             /* bf16 weights, bf16-pair activations, fp32 accumulate     */
 } wf_precision;
 

@@ -3,7 +3,6 @@
 // the step loop and of the transforms.
 #pragma once
 
-#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <vector>
@@ -48,29 +47,26 @@ inline float bf16_value_of(float v) {
     return r;
 }
 
-// f16 bits of v, round to nearest even (finite values past its range become
-// infinities, NaN stays one).
-inline uint16_t f16_round(float v) {
-    uint32_t u;
-    std::memcpy(&u, &v, 4);
-    const uint32_t s = (u >> 16) & 0x8000u;
-    u &= 0x7fffffffu;
-    if (u > 0x7f800000u) return (uint16_t)(s | 0x7e00u);
-    if (u >= 0x477ff000u) return (uint16_t)(s | 0x7c00u);       // rounds to 2^16 or more
-    if (u < 0x38800000u) {                                       // below 2^-14: units of 2^-24
-        float a;
-        std::memcpy(&a, &u, 4);
-        return (uint16_t)(s | (uint32_t)std::nearbyint(a * 16777216.0f));
+// v as the exact sum of three bf16 values of falling size (not finite: itself
+// and zeros).
+inline void bf16_parts(float v, uint16_t (&p)[3]) {
+    for (int n = 0; n < 3; ++n) {
+        uint32_t u;
+        std::memcpy(&u, &v, 4);
+        p[n] = bf16_round(v);
+        if ((p[n] & 0x7f80) == 0x7f80) {   // not finite, or rounded past the range: cut off instead
+            p[n] = (uint16_t)(u >> 16);
+            if ((u & 0x7fffffffu) > 0x7f800000u) p[n] |= 0x40;   // (a NaN stays one)
+            if ((u & 0x7f800000u) == 0x7f800000u) {
+                for (++n; n < 3; ++n) p[n] = 0;
+                return;
+            }
+        }
+        u = (uint32_t)p[n] << 16;
+        float h;
+        std::memcpy(&h, &u, 4);
+        v -= h;
     }
-    u += 0xfffu + ((u >> 13) & 1u);
-    return (uint16_t)(s | ((u - 0x38000000u) >> 13));
-}
-
-// The value of f16 bits (finite or infinite).
-inline float f16_value_of(uint16_t h) {
-    const int e = (h >> 10) & 31, m = h & 0x3ff;
-    const float a = e == 31 ? INFINITY : (e ? std::ldexp((float)(m + 1024), e - 25) : std::ldexp((float)m, -24));
-    return h & 0x8000 ? -a : a;
 }
 
 // The same for bf16 operands, k-blocks of 32: lane l holds

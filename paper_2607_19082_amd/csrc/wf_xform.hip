@@ -23,7 +23,6 @@
 // rows are input pixels, columns (class, channel), k the 3x3 input
 // neighbourhood (taps a class does not use have zero weights), so one
 // 16-column tile carries all 12 outputs of an input pixel.
-#include <cmath>
 #include <utility>
 #include <vector>
 
@@ -40,9 +39,6 @@ struct Layer {
     int mode, Ci, Co, Cop, relu;
     const void* wp[4];
     const float* bias;        // h_s: [Co]; g_s: [Cop] (GDN: beta)
-    const int* ce;            // g_s, fp32: [Cop] scale exponents of the weight columns
-    int force_f32;            // g_s, fp32: a weight is not finite
-    float covered;            // inverse GDN, fp32: see SynthArgs
 };
 
 struct Xform {
@@ -100,16 +96,14 @@ static int xf_pack_synth(Xform* x, Layer& L, int nclass, int ncol, F wt, G bias)
         nkx = L.mode == XM_GDN ? 1 : (L.mode == XM_DECONV && (c & 1) ? 2 : 3);
         return nkx * (L.mode == XM_GDN ? 1 : (L.mode == XM_DECONV && (c >> 1) ? 2 : 3));
     };
-    std::vector<int> ce;
     std::vector<uint16_t> v[4];
-    L.force_f32 = pack_split(x->precision == WF_BF16, nclass, L.Ci, ncol, L.Cop, ntap, wt, ce, v);
+    pack_split(x->precision == WF_BF16, nclass, L.Ci, ncol, L.Cop, ntap, wt, v);
     int rc = WF_OK;
     for (int c = 0; c < nclass && rc == WF_OK; ++c) rc = xf_upload(x, reinterpret_cast<const uint16_t**>(&L.wp[c]), v[c]);
     for (int c = nclass; c < 4; ++c) L.wp[c] = L.wp[0];
     std::vector<float> bv(L.Cop, 0.0f);
     for (int n = 0; n < ncol; ++n) bv[n] = bias(n);
-    if (rc == WF_OK) rc = xf_upload(x, &L.bias, bv);
-    return rc != WF_OK ? rc : xf_upload(x, &L.ce, ce);
+    return rc != WF_OK ? rc : xf_upload(x, &L.bias, bv);
 }
 
 // Transposed conv weight W[ci][co][5][5]: tap t of class (py, px) is
@@ -159,15 +153,6 @@ static int xf_conv3(Xform* x, Layer& L, const float* w, const float* b, int Ci, 
 }
 
 static int xf_synth_gdn(Xform* x, Layer& L, const float* beta, const float* gamma, int C) {
-    // an error of 2^-38 of the patch's largest square in each of them adds at
-    // most 2^-38 max sum_j gamma_cj to z_c; 2^-23 beta_c or less counts as covered
-    double cov = 3e38;
-    for (int c = 0; c < C; ++c) {
-        double sum = 0.0;
-        for (int j = 0; j < C; ++j) sum += std::fabs((double)gamma[(size_t)c * C + j]);
-        cov = std::fmin(cov, 32768.0 * std::fabs((double)beta[c]) / sum);
-    }
-    L.covered = cov > 0.0 ? (float)cov : 0.0f;
     L.mode = XM_GDN; L.Ci = C; L.Co = C; L.Cop = (C + kTile - 1) / kTile * kTile; L.relu = 0;
     return xf_pack_synth(x, L, 1, C, [&](int, int, int, int j, int c) { return gamma[(size_t)c * C + j]; },
                          [&](int n) { return beta[n]; });
@@ -250,7 +235,7 @@ static void launch_synth(SynthArgs a, hipStream_t st) {
 
 static SynthArgs synth_args(const Layer& L, const float* in, float* out, int B, int h, int w) {
     SynthArgs a{};
-    a.in = in; a.out = out; a.bias = L.bias; a.ce = L.ce; a.force_f32 = L.force_f32; a.covered = L.covered;
+    a.in = in; a.out = out; a.bias = L.bias;
     for (int c = 0; c < 4; ++c) a.wp[c] = L.wp[c];
     a.Ci = L.Ci; a.Co = L.Co; a.Cop = L.Cop; a.nch = ceil_div(L.Ci, 32);
     a.B = B; a.Hi = h; a.Wi = w; a.Ho = 2 * h; a.Wo = 2 * w; a.ncls = L.mode == XM_DECONV ? 4 : 1;
@@ -259,7 +244,7 @@ static SynthArgs synth_args(const Layer& L, const float* in, float* out, int B, 
 
 // A transposed conv and its inverse GDN, [B][h][w][Ci] -> [B][2h][2w][Co]:
 // in one kernel into `other` where a workgroup of 128 pixels holds every
-// channel (up to 192) and the grid gives every compute unit a workgroup.
+// channel (up to 192) and the layer has enough of them.
 // Otherwise the conv writes `other` and the GDN `own`, the buffer that may hold
 // the conv's input.  Returns the output.
 template <class P>
@@ -267,8 +252,8 @@ static float* run_synth(const Layer& L, const Layer& G, const float* in, float* 
                         hipStream_t st) {
     SynthArgs a = synth_args(L, in, other, B, h, w);
     const long long nb = 4LL * B * h * w / 128;
-    if (nb >= kSynthMinBlocks && L.Cop <= 192) {
-        a.gwp = G.wp[0]; a.gce = G.ce; a.beta = G.bias; a.gforce = G.force_f32; a.covered = G.covered;
+    if (nb >= kSynthMinBlocks<P> && L.Cop <= 192) {
+        a.gwp = G.wp[0]; a.beta = G.bias;
         if (L.Cop <= 128) launch_synth<P, XM_DECONV, 8, 2, 4, true>(a, st);
         else launch_synth<P, XM_DECONV, 8, 3, 4, true>(a, st);
         return other;
@@ -276,7 +261,7 @@ static float* run_synth(const Layer& L, const Layer& G, const float* in, float* 
     SynthArgs g = synth_args(G, other, own, 1, 1, B * 4 * h * w);
     g.Ho = 1;
     g.Wo = g.Wi;
-    if (nb * ceil_div(L.Cop, 192) >= kSynthMinBlocks) {
+    if (nb * ceil_div(L.Cop, 192) >= kSynthMinBlocks<P>) {
         launch_synth<P, XM_DECONV, 8, 3, 4>(a, st);
         launch_synth<P, XM_GDN, 8, 3, 4>(g, st);
     } else {
@@ -384,7 +369,7 @@ int wf_synthesis(wf_xform_t plan, const float* y_hat, float* image, hipStream_t 
     if (!plan || !y_hat || !image) return fail(WF_E_INVALID, "plan, y_hat or image is NULL");
     const Xform& x = *reinterpret_cast<Xform*>(plan);
     if (x.precision == WF_BF16) synth<SBF16>(x, y_hat, image, stream);
-    else synth<SF16>(x, y_hat, image, stream);
+    else synth<SF32>(x, y_hat, image, stream);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? WF_OK : xf_fail_hip(e, "transform launch");
 }
