@@ -68,11 +68,16 @@ struct SBF16 {                // bf16 transform: bf16 weights, bf16-pair activat
 template <class P>
 constexpr bool kSplit3 = P::kNw == 3;
 
-// Workgroups of 128 pixels from which they are the faster ones (fp32, whole
-// transform of a 16x16 latent, whose third layer has 128 of them: 139 us, with
-// 64 x 64 tiles there 113; 50x75, second layer 468: 488 and 486).
+// Workgroups of 128 pixels in a layer from which they are the faster ones (two
+// fit a compute unit).  us of a whole transform with that layer in 128 x 192
+// tiles, inverse GDN in them, and in 64 x 64, for layers of this many of them.
+// fp32 (N = 128 unless said): 192 250 / 232, 300 365 / 355, 320 154 / 151, 325
+// 1228 / 1215 (N = 192 2488 / 2418), 432 169 / 171 (N = 192 293 / 301), 468
+// 488 / 486 (938 / 942), 675 653 / 671.  bf16: 192 138 / 128, 255 482 / 458
+// (898 / 866), 300 183 / 183, 320 104 / 102, 325 610 / 589 (1118 / 1137), 432
+// 107 / 116, 468 244 / 251.
 template <class P>
-constexpr int kSynthMinBlocks = 256;
+constexpr int kSynthMinBlocks = kSplit3<P> ? 432 : 320;
 
 // Parts of eight values.  Three: x0 cut off after eight bits (rounded it could
 // overflow), x1 rounded, x2 what is left; two: rounded, and the rest rounded.
