@@ -342,8 +342,10 @@ def test_resident_replicas(name, B, H, W, precision, grid):
     ("cheng-gmm3-1080p-120x68-m192", 3, 33, 40, "fp32", 192),
     ("minnen-16x16-m192", 6, 33, 20, "fp32", 128),                # four replicas, parts split over four waves
     ("minnen-16x16-m192", 6, 33, 20, "fp32", 64),
+    ("minnen-16x16-m192", 6, 18, 17, "fp32", 160),                # three replicas
     ("minnen-hr-4k-240x135-m320", 5, 17, 9, "fp32", 320),
     ("minnen-16x16-m192", 6, 18, 17, "bf16", 192),
+    ("minnen-16x16-m192", 6, 18, 17, "bf16", 256),                # three replicas leave no slots for the hoist in the launch
 ])
 def test_resident_bits_alone_and_in_a_batch(name, B, H, W, precision, M):
     """An image's bits are the same in a batch, alone, beside other images and

@@ -287,9 +287,9 @@ def test_synthesis_not_finite(value, where, H, W):
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 def test_synthesis_not_finite_in_a_halo(value, H, W):
     """A value that is not finite in the grid's last latent: workgroups whose
-    patch only touches it in its halo leave the f16 products too (beside the
-    next reduction of the workgroup), and every pixel out of its reach is as
-    far from the oracle as without it; three calls give the same bits."""
+    patch only touches it in its halo may compute a tile again on fp32 products
+    too, wave by wave, and every pixel out of its reach is as far from the
+    oracle as without it; three calls give the same bits."""
     N, M = 32, 32
     w = inputs.make_transform_weights(N, M)
     y = np.random.default_rng(12).normal(scale=2.0, size=(1, H, W, M)).astype(np.float32)
