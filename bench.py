@@ -63,7 +63,7 @@ def leg_kernel(k, driver):
 
 
 # sources that no decode from symbols runs (the transforms, the entropy coder)
-NOT_DECODE = ("wf_xform.hip", "wf_ec.hip")
+NOT_DECODE = ("wf_xform.hip", "wf_split.h", "wf_ec.hip")
 
 
 def source_hash():

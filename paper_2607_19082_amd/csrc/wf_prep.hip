@@ -1,7 +1,4 @@
-// What a call of the resident driver needs before its launch of k_resident
-// (in a file of its own: the code of the roles then lies in memory as it was
-// measured; with these kernels beside them the 1080p mixture decode, whose
-// roles are the largest, took 5.38 ms instead of 5.29).
+// What a call of the resident driver needs before its launch of k_resident.
 #include <algorithm>
 
 #include "wf_conv.h"

@@ -1092,9 +1092,10 @@ __device__ __noinline__ void res_l3(const StepArgs& a_in, const ResArgs& r_in, i
         if constexpr (MEAN && KC == 3 && !P::kBf16) {
             // y_hat first, and counted before the outputs that no role reads
             // are stored: the 1080p mixture decode 5.30 -> 4.74 ms.  (K = 1
-            // has one such output and is no faster that way.  bf16 keeps its
-            // code: the roles after it in memory then stay where they were
-            // measured, moved they took 1% longer.)
+            // has one such output and is no faster that way.  The bf16 mixture
+            // is slower that way: 1080p 3.21 -> 3.33 ms, three images 4.08 ->
+            // 4.18, 48x32 1.33 -> 1.37.  It stores in the order further down;
+            // one epilogue for both, the order a constant, took bf16 3.24 ms.)
             const float mx = fmaxf(o[0], fmaxf(o[1], o[2]));
             float wk[3], den = 0.0f, mu = 0.0f;
 #pragma unroll
