@@ -39,9 +39,9 @@ namespace wf {
 // each weight operand feeds RT MFMA chains and each activation operand CT.
 // Weights are the first MFMA operand: a lane then holds four consecutive
 // channels of one pixel and stores 16 bytes.  4K (N = 192, M = 320): 20.36 ms
-// with per-wave operand loads and fp32 MFMA, 7.1 ms now (the third layer
+// with per-wave operand loads and fp32 MFMA, 7.2 ms now (the third layer
 // with its inverse GDN 4.9 ms, 225 TFLOP/s of fp32 products, 1350 of bf16 ones,
-// the matrix cores busy 68%); bf16 at 120x68 latents (N = 128): 1.98 -> 0.44 ms.
+// the matrix cores busy 68%); bf16 at 120x68 latents (N = 128): 1.98 -> 0.45 ms.
 struct SynthArgs {
     const float* in;
     float* out;
