@@ -90,7 +90,9 @@ typedef enum {
                                WF_E_UNSUPPORTED when the slices do not fit the registers
                                or the compute units, M is not a multiple of 32 or the
                                schedule has more than 4095 steps; calls need y_hat
-                               aligned to 128 bytes (WF_E_INVALID otherwise).  fp32:
+                               aligned to 128 bytes (WF_E_INVALID otherwise).  An image's
+                               outputs have the same bits alone, at any place of a batch
+                               and whatever rows follow below.  fp32:
                                layer-1 and -2 outputs are read until no value holds an
                                all-ones fill word, a NaN that finite inputs never yield;
                                inputs holding NaNs with that exact bit pattern can make
